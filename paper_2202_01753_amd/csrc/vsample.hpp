@@ -60,27 +60,73 @@ __device__ __forceinline__ auto axis_consts(CP base, int j) {
 // advanced by the Weyl constants between rounds.  The key is uniform across
 // the wavefront, so its schedule stays in scalar registers.  Each round's two
 // three-way XORs are single v_bitop3_b32 instructions (truth table 0x96 is
-// a ^ b ^ c); in the first round the counter words x1, x3 are uniform or fixed
-// per sub-cube, so there the compiler folds their XOR with the key instead.
+// a ^ b ^ c).
+//
+// Of a block's counter (c, iteration, t_lo, t_hi) only t_lo differs between
+// the lanes of a wavefront (see uniform_hi), and of the blocks of a sub-cube
+// only c, so the first rounds split into what the sub-cube's blocks share
+// (PhiloxCube, once per sub-cube) and what is uniform (scalar instructions):
+// a block is left with the two XORs of round 2, two products and two XORs in
+// round 3, and two of each in rounds 4 to 10, 16 products instead of 20.
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-__device__ __forceinline__ void philox4x32_10(uint32_t &x0, uint32_t &x1, uint32_t &x2,
-                                              uint32_t &x3, uint32_t k0, uint32_t k1) {
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
+constexpr uint32_t kWeyl0 = 0x9E3779B9u, kWeyl1 = 0xBB67AE85u;
+
+// The upper half of the sub-cube index, uniform across the wavefront: the
+// lanes of a wave hold consecutive indices that start at a multiple of their
+// number, so they never straddle a multiple of 2^32.
+__device__ __forceinline__ uint32_t uniform_hi(uint64_t t) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(t >> 32));
+}
+
+// What every block of sub-cube t shares: the low word of round 1's second
+// product, and both words of round 2's first.
+struct PhiloxCube {
+    uint32_t b1, h2, l2;
+};
+
+__device__ __forceinline__ PhiloxCube philox_cube(uint32_t tlo, uint32_t iter, uint32_t k0) {
+    const uint64_t pb = (uint64_t)kPhiloxM1 * (uint64_t)tlo;
+    const uint64_t pa = (uint64_t)kPhiloxM0 * (uint64_t)((uint32_t)(pb >> 32) ^ (iter ^ k0));
+    return PhiloxCube{(uint32_t)pb, (uint32_t)(pa >> 32), (uint32_t)pa};
+}
+
+// Block c of a sub-cube: w[0..3].  c and thi are uniform.
+__device__ __forceinline__ void philox_block(const PhiloxCube &q, uint32_t c, uint32_t thi, uint32_t k0,
+                                             uint32_t k1, uint32_t *w) {
+    // round 1 and round 2's second product: scalar
+    const uint64_t pa1 = (uint64_t)kPhiloxM0 * (uint64_t)c;
+    const uint64_t pb2 = (uint64_t)kPhiloxM1 * (uint64_t)((uint32_t)(pa1 >> 32) ^ thi ^ k1);
+    k0 += kWeyl0;
+    k1 += kWeyl1;
+    uint32_t x0 = q.b1 ^ ((uint32_t)(pb2 >> 32) ^ k0);
+    uint32_t x2 = q.h2 ^ ((uint32_t)pa1 ^ k1);
+    k0 += kWeyl0;
+    k1 += kWeyl1;
+    // round 3
+    uint64_t pa = (uint64_t)kPhiloxM0 * (uint64_t)x0;
+    uint64_t pb = (uint64_t)kPhiloxM1 * (uint64_t)x2;
+    x0 = (uint32_t)(pb >> 32) ^ ((uint32_t)pb2 ^ k0);
+    x2 = xor3((uint32_t)(pa >> 32), q.l2, k1);
+    uint32_t x1 = (uint32_t)pb, x3 = (uint32_t)pa;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t pa = (uint64_t)0xD2511F53u * (uint64_t)x0;
-        const uint64_t pb = (uint64_t)0xCD9E8D57u * (uint64_t)x2;
-        const uint32_t y0 = r == 0 ? (uint32_t)(pb >> 32) ^ (x1 ^ k0) : xor3((uint32_t)(pb >> 32), x1, k0);
-        const uint32_t y2 = r == 0 ? (uint32_t)(pa >> 32) ^ (x3 ^ k1) : xor3((uint32_t)(pa >> 32), x3, k1);
+    for (int r = 3; r < 10; ++r) {
+        k0 += kWeyl0;
+        k1 += kWeyl1;
+        pa = (uint64_t)kPhiloxM0 * (uint64_t)x0;
+        pb = (uint64_t)kPhiloxM1 * (uint64_t)x2;
+        x0 = xor3((uint32_t)(pb >> 32), x1, k0);
+        x2 = xor3((uint32_t)(pa >> 32), x3, k1);
         x1 = (uint32_t)pb;
         x3 = (uint32_t)pa;
-        x0 = y0;
-        x2 = y2;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
     }
+    w[0] = x0;
+    w[1] = x1;
+    w[2] = x2;
+    w[3] = x3;
 }
 
 // (2X+1) 2^-53 for the 52-bit X = (whi << 20) | (wlo >> 12): the double with
@@ -402,7 +448,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     R cd[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) cd[j] = R(dig[j]);
-    const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
+    const uint32_t thi = uniform_hi(t);
+    const PhiloxCube pc = philox_cube((uint32_t)t, a.iter, k0);
     const bool traced = TRACE && (int64_t)t >= a.t0 && (int64_t)t < a.t1;
 
     double I0 = 0.0, S1 = 0.0, S2 = 0.0;
@@ -416,14 +463,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             __builtin_amdgcn_s_setprio(1);
             uint32_t w[4 * NUSED];
 #pragma unroll
-            for (int b = 0; b < NUSED; ++b) {
-                uint32_t x0 = (uint32_t)(k * NBLK + b), x1 = a.iter, x2 = tlo, x3 = thi;
-                philox4x32_10(x0, x1, x2, x3, k0, k1);
-                w[4 * b] = x0;
-                w[4 * b + 1] = x1;
-                w[4 * b + 2] = x2;
-                w[4 * b + 3] = x3;
-            }
+            for (int b = 0; b < NUSED; ++b)
+                philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
             R J = R(1);
 #pragma unroll
@@ -532,14 +573,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(GF ? 2 : 1);
             uint32_t w[4 * NUSED];
 #pragma unroll
-            for (int b = 0; b < NUSED; ++b) {
-                uint32_t x0 = (uint32_t)(k * NBLK + b), x1 = a.iter, x2 = tlo, x3 = thi;
-                philox4x32_10(x0, x1, x2, x3, k0, k1);
-                w[4 * b] = x0;
-                w[4 * b + 1] = x1;
-                w[4 * b + 2] = x2;
-                w[4 * b + 3] = x3;
-            }
+            for (int b = 0; b < NUSED; ++b)
+                philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
             int bin[D];
             R J = R(1);

@@ -36,12 +36,17 @@ __device__ __forceinline__ void run_segment(Const<SampleArgs> &a, const BatchSeg
 #pragma unroll
         for (int j = 0; j < D; ++j) step[j] = (int32_t)sd[j];
     }
-    uint64_t t = (uint64_t)sg.t0 + threadIdx.x;
+    // the segment, its ends rounded up to multiples of 64 (the integral's first
+    // and last end stay): a wave then holds 64 consecutive sub-cubes that
+    // start at a multiple of 64 (uniform_hi)
+    const uint64_t t0 = ((uint64_t)sg.t0 + 63u) & ~63ull;
+    const uint64_t t1 = min(((uint64_t)sg.t1 + 63u) & ~63ull, (uint64_t)a.m);
+    uint64_t t = t0 + threadIdx.x;
     uint32_t dig[D];
     digits_of<D>(t, g, dig);
     double sI = 0.0, cI = 0.0, sV = 0.0, cV = 0.0;
     bool bad = false;
-    while (t < (uint64_t)sg.t1) {
+    while (t < t1) {
         double It, vt;
         // (plain, not volatile, constant loads: measured faster here, where
         // the cases' shared register allocation is set by other values; one
