@@ -162,6 +162,23 @@ __device__ __forceinline__ float rmax(float a, float b) { return fmaxf(a, b); }
 __device__ __forceinline__ double rexp(double a) { return exp(a); }
 __device__ __forceinline__ float rexp(float a) { return expf(a); }
 
+// The bin of the stratified coordinate z >= 0 (in bins) and the fraction inside
+// it, the bin clamped to the last one and the fraction to 1 there: once
+// z >= nb, z - (nb-1) is at least 1 and the clamp makes it exactly 1; otherwise
+// z - floor(z) < 1 is exact.  The clamp to [0, 1] is the output modifier of
+// the subtraction, free.  FP64 truncates to the integer first and converts
+// back (floor and a FP64 minimum would cost 2 cycles more than the integer
+// minimum and the conversion); in FP32 floor and minimum are the cheaper half.
+__device__ __forceinline__ double bin_of(double z, int last, double, int &i) {
+    i = min((int)z, last);
+    return fmin(fmax(z - (double)i, 0.0), 1.0);
+}
+__device__ __forceinline__ float bin_of(float z, int, float lastf, int &i) {
+    const float fz = rmin(rfloor(z), lastf);
+    i = (int)fz;
+    return fminf(fmaxf(z - fz, 0.0f), 1.0f);
+}
+
 // ---------------------------------------------------------------- integrands
 
 template <typename R>
@@ -439,7 +456,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
     const int nb = a.nb, row = nb + 1, rec = 3 * D + 2;
     const R s = R(F32 ? a.s32 : a.s);
-    const R last = R(nb - 1);
+    const int last = nb - 1;
+    const R lastr = R(last);
     const R *sG = v.grid;
     // with two histogram copies the upper half of each wave adds into the
     // second, so at most half as many lanes add into one bin at once
@@ -473,12 +491,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 if constexpr (F32) u = uniform24(w[j]);
                 else u = uniform53(w[j], w[D + j]);
                 const R z = (cd[j] + u) * s;
-                // bin index, clamped to the last bin with fraction 1 there: once
-                // floor(z) > nb-1 we have z >= nb, so z - (nb-1) >= 1 and the min
-                // gives exactly 1; otherwise z - floor(z) < 1 is exact.
-                const R fz = rmin(rfloor(z), last);
-                const int i = (int)fz;
-                const R frac = rmin(z - fz, R(1));
+                int i;
+                const R frac = bin_of(z, last, lastr, i);
                 R left, width;
                 if constexpr (F32) {
                     const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + i];
@@ -590,9 +604,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     if constexpr (F32) uj = uniform24(w[j]);
                     else uj = uniform53(w[j], w[D + j]);
                     const R z = (cd[j] + uj) * s;
-                    const R fz = rmin(rfloor(z), last);
-                    gf_bin[j] = (int)fz;
-                    gf_frac[j] = rmin(z - fz, R(1));
+                    gf_frac[j] = bin_of(z, last, lastr, gf_bin[j]);
                     if constexpr (F32) {
                         const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + gf_bin[j]];
                         gf_left[j] = cell.x;
@@ -624,12 +636,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     if constexpr (F32) u = uniform24(w[j]);
                     else u = uniform53(w[j], w[D + j]);
                     const R z = (cd[j] + u) * s;
-                    // bin index, clamped to the last bin with fraction 1 there: once
-                    // floor(z) > nb-1 we have z >= nb, so z - (nb-1) >= 1 and the min
-                    // gives exactly 1; otherwise z - floor(z) < 1 is exact.
-                    const R fz = rmin(rfloor(z), last);
-                    i = (int)fz;
-                    frac = rmin(z - fz, R(1));
+                    frac = bin_of(z, last, lastr, i);
                     if constexpr (F32) {
                         const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + i];
                         left = cell.x;
