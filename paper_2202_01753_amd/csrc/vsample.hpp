@@ -248,28 +248,45 @@ struct TableCell {
 template <typename R>
 constexpr int kTableStride = std::is_same<R, float>::value ? 2 * kTableN * kTableN : kTableN * kTableN;
 
+// The cell of a table coordinate u (in nodes) and the offset in it, the edge
+// cell extended outside [0, 255].  FP64 truncates, clamps the integer and
+// converts it back (truncation differs from floor only below 0, where the
+// clamp makes both 0), one instruction less than floor and two FP64 clamps; in
+// FP32 floor and the three-way median are the cheaper half.
+__device__ __forceinline__ int table_axis(double u, double &t) {
+    const int a = min(max((int)u, 0), kTableN - 2);
+    t = u - (double)a;
+    return a;
+}
+__device__ __forceinline__ int table_axis(float u, float &t) {
+    const float fa = rmin(rmax(rfloor(u), 0.0f), (float)(kTableN - 2));
+    t = u - fa;
+    return (int)fa;
+}
+
 template <typename R>
 __device__ __forceinline__ TableCell<R> table_cell(const R *__restrict__ T, R x, R y) {
-    const R ux = x * R(255), uy = y * R(255);
-    const R fa = rmin(rmax(rfloor(ux), R(0)), R(254));
-    const R fb = rmin(rmax(rfloor(uy), R(0)), R(254));
-    const int cell = (int)fa * kTableN + (int)fb;
     TableCell<R> c;
-    c.tx = ux - fa;
-    c.ty = uy - fb;
+    const int a = table_axis(x * R(kTableN - 1), c.tx);
+    const int b = table_axis(y * R(kTableN - 1), c.ty);
+    // a 32-bit byte offset from the uniform base: one scalar and one vector
+    // address register, no 64-bit address arithmetic
+    const uint32_t off = (uint32_t)(a * kTableN + b) * 8u;
+    const char *base = reinterpret_cast<const char *>(T);
     if constexpr (std::is_same<R, float>::value) {
         // two 8-byte-aligned pairs, which the compiler merges into one load
-        const float2 *q = reinterpret_cast<const float2 *>(T + 2 * cell);
+        const float2 *q = reinterpret_cast<const float2 *>(base + off);
         const float2 lo = q[0], hi = q[1];
         c.t00 = lo.x;
         c.t10 = lo.y;
         c.t01 = hi.x;
         c.t11 = hi.y;
     } else {
-        c.t00 = T[cell];
-        c.t01 = T[cell + 1];
-        c.t10 = T[cell + kTableN];
-        c.t11 = T[cell + kTableN + 1];
+        const double *q = reinterpret_cast<const double *>(base + off);
+        c.t00 = q[0];
+        c.t01 = q[1];
+        c.t10 = q[kTableN];
+        c.t11 = q[kTableN + 1];
     }
     return c;
 }
