@@ -254,7 +254,9 @@ constexpr int kTableStride = std::is_same<R, float>::value ? 2 * kTableN * kTabl
 // clamp makes both 0), one instruction less than floor and two FP64 clamps; in
 // FP32 floor and the three-way median are the cheaper half.
 __device__ __forceinline__ int table_axis(double u, double &t) {
-    const int a = min(max((int)u, 0), kTableN - 2);
+    int a;  // the instruction itself: it saturates, where C++ leaves large u and NaN undefined
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(a) : "v"(u));
+    a = min(max(a, 0), kTableN - 2);
     t = u - (double)a;
     return a;
 }
@@ -410,6 +412,53 @@ struct LdsView {
     }
 };
 
+// LDS addresses.  A sample's bin on axis j is one 8-byte grid entry (FP64: the
+// left boundary, followed by the right one; FP32: the float pair), whose LDS
+// address also leads to the bin's histogram entry: row j of the grid starts j
+// entries further into its region in FP64 (rows of nb + 1) than row j of the
+// histogram, and not at all in FP32 (rows of nb), so the histogram entry lies
+// at a distance from the grid entry that is the same for every bin and axis up
+// to an instruction offset of 8 (D - 1 - j) bytes (to_hist).  One two-cycle
+// addition per contribution replaces a four-cycle shift-and-add.
+using LdsDouble = __attribute__((address_space(3))) double;
+using LdsWord = __attribute__((address_space(3))) uint64_t;
+
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)(const char *)p;
+}
+
+// The LDS address of entry i of a grid row that starts at row_address; opaque,
+// so that the address is kept rather than formed again for the histogram.
+__device__ __forceinline__ uint32_t cell_address(uint32_t row_address, int i) {
+    uint32_t a = row_address + ((uint32_t)i << 3);
+    asm("" : "+v"(a));
+    return a;
+}
+
+// A grid entry as it lies in LDS: the left boundary and the right one (FP64)
+// or the width (FP32); read_cell gives the width in both.
+__device__ __forceinline__ void load_cell(uint32_t cell, double &left, double &right) {
+    const LdsDouble *B = (const LdsDouble *)cell;
+    left = B[0];
+    right = B[1];
+}
+__device__ __forceinline__ void load_cell(uint32_t cell, float &left, float &width) {
+    const uint64_t B = *(const LdsWord *)cell;  // one 8-byte read
+    left = __uint_as_float((uint32_t)B);
+    width = __uint_as_float((uint32_t)(B >> 32));
+}
+template <typename R>
+__device__ __forceinline__ void read_cell(uint32_t cell, R &left, R &width) {
+    load_cell(cell, left, width);
+    if constexpr (!std::is_same<R, float>::value) width = width - left;
+}
+
+template <int D, bool F32>
+__device__ __forceinline__ void add_bin(uint32_t cell, uint32_t to_hist, int j, double v) {
+    LdsDouble *h = (LdsDouble *)(cell + to_hist) + (F32 ? 0 : D - 1 - j);
+    __hip_atomic_fetch_add(h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Copies the integral's grid into LDS and clears the histogram.  Callers
 // synchronise the workgroup afterwards.  (A is SampleArgs, possibly in the
 // constant address space: see the batched kernel.)
@@ -512,14 +561,16 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     constexpr int NBLK = (D + 1) / 2;                      // blocks in the counter layout
     constexpr int NUSED = F32 ? (D + 3) / 4 : NBLK;        // blocks this precision needs
     const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const int nb = a.nb, row = nb + 1, rec = 3 * D + 2;
+    const int nb = a.nb, row = F32 ? nb : nb + 1, rec = 3 * D + 2;
     const R s = R(F32 ? a.s32 : a.s);
     const int last = nb - 1;
     const R lastr = R(last);
-    const R *sG = v.grid;
-    // with two histogram copies the upper half of each wave adds into the
-    // second, so at most half as many lanes add into one bin at once
-    double *sH = v.hist + (a.hist_copies > 1 && (threadIdx.x & 32) ? D * a.nb : 0);
+    const uint32_t grid0 = lds_address(v.grid), row_bytes = (uint32_t)row * 8u;
+    // from a grid entry to its bin's histogram entry (see above); with two
+    // histogram copies the upper half of each wave adds into the second, so at
+    // most half as many lanes add into one bin at once
+    uint32_t to_hist = lds_address(v.hist) - grid0 - (F32 ? 0u : 8u * (D - 1));
+    if (a.hist_copies > 1 && (threadIdx.x & 32)) to_hist += (uint32_t)(D * nb) * 8u;
 
     R cd[D];
 #pragma unroll
@@ -530,8 +581,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
 
     double I0 = 0.0, S1 = 0.0, S2 = 0.0;
     if constexpr (PAIR) {
-        // One sample: its value I_k and its bin on every axis (and its trace record).
-        auto point = [&](int k, int (&bin)[D]) -> double {
+        // One sample: its value I_k and its grid cell on every axis (and its trace record).
+        auto point = [&](int k, uint32_t (&cell)[D]) -> double {
             // raised wave priority while the sample's random words, bins and
             // grid reads are formed, back to normal before its integrand
             // value (see the one-sample path below; FP32-eval Gaussian and
@@ -551,16 +602,9 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const R z = (cd[j] + u) * s;
                 int i;
                 const R frac = bin_of(z, last, lastr, i);
+                cell[j] = cell_address(grid0 + j * row_bytes, i);
                 R left, width;
-                if constexpr (F32) {
-                    const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + i];
-                    left = cell.x;
-                    width = cell.y;
-                } else {
-                    const R *B = sG + j * row + i;
-                    left = B[0];
-                    width = B[1] - left;
-                }
+                read_cell(cell[j], left, width);
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
                 R xj;
@@ -569,7 +613,6 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 else
                     xj = rfma(cj[1], xu, cj[0]);
                 J = J * (width * cj[2]);
-                bin[j] = i;
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -598,13 +641,13 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             S1 = S1 + dev;
             S2 = __fma_rn(dev, dev, S2);
         };
-        auto add_bins = [&](const int (&bin)[D], double Ik) {
+        auto add_bins = [&](const uint32_t (&cell)[D], double Ik) {
             if (a.hist) {
                 const double sq = Ik * Ik;
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) atomicAdd(&sH[j * nb + bin[j]], sq);
+                    if (j < axes) add_bin<D, F32>(cell[j], to_hist, j, sq);
             }
         };
         {
@@ -612,19 +655,19 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             // atomics, so that the two evaluations can interleave
             int k = 0;
             for (; k + 1 < a.p; k += 2) {
-                int bin0[D], bin1[D];
-                const double Ia = point(k, bin0);
-                const double Ib = point(k + 1, bin1);
+                uint32_t cell0[D], cell1[D];
+                const double Ia = point(k, cell0);
+                const double Ib = point(k + 1, cell1);
                 accumulate(k, Ia);
                 accumulate(k + 1, Ib);
-                add_bins(bin0, Ia);
-                add_bins(bin1, Ib);
+                add_bins(cell0, Ia);
+                add_bins(cell1, Ib);
             }
             if (k < a.p) {
-                int bin0[D];
-                const double Ia = point(k, bin0);
+                uint32_t cell0[D];
+                const double Ia = point(k, cell0);
                 accumulate(k, Ia);
-                add_bins(bin0, Ia);
+                add_bins(cell0, Ia);
             }
         }
     } else {
@@ -648,13 +691,12 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             for (int b = 0; b < NUSED; ++b)
                 philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
-            int bin[D];
+            uint32_t cell[D];
             R J = R(1);
             // GF: every axis's bin and grid read first, then the rest axis by
             // axis, so that the grid reads are in flight together rather
             // than each waited for before the next is issued (see kGridFirst)
             R gf_frac[GF ? D : 1], gf_left[GF ? D : 1], gf_right[GF ? D : 1];
-            int gf_bin[GF ? D : 1];
             if constexpr (GF) {
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
@@ -662,16 +704,10 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     if constexpr (F32) uj = uniform24(w[j]);
                     else uj = uniform53(w[j], w[D + j]);
                     const R z = (cd[j] + uj) * s;
-                    gf_frac[j] = bin_of(z, last, lastr, gf_bin[j]);
-                    if constexpr (F32) {
-                        const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + gf_bin[j]];
-                        gf_left[j] = cell.x;
-                        gf_right[j] = cell.y;  // FP32-eval grids hold the width here
-                    } else {
-                        const R *B = sG + j * row + gf_bin[j];
-                        gf_left[j] = B[0];
-                        gf_right[j] = B[1];
-                    }
+                    int i;
+                    gf_frac[j] = bin_of(z, last, lastr, i);
+                    cell[j] = cell_address(grid0 + j * row_bytes, i);
+                    load_cell(cell[j], gf_left[j], gf_right[j]);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of their uses
                 if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
@@ -679,13 +715,11 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
 #pragma unroll
             for (int j = 0; j < D; ++j) {
                 R u = R(0), frac, left, width;
-                int i;
                 if constexpr (GF) {
                     if (traced) {
                         if constexpr (F32) u = uniform24(w[j]);
                         else u = uniform53(w[j], w[D + j]);
                     }
-                    i = gf_bin[j];
                     frac = gf_frac[j];
                     left = gf_left[j];
                     if constexpr (F32) width = gf_right[j];
@@ -694,16 +728,10 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     if constexpr (F32) u = uniform24(w[j]);
                     else u = uniform53(w[j], w[D + j]);
                     const R z = (cd[j] + u) * s;
+                    int i;
                     frac = bin_of(z, last, lastr, i);
-                    if constexpr (F32) {
-                        const float2 cell = reinterpret_cast<const float2 *>(sG)[j * nb + i];
-                        left = cell.x;
-                        width = cell.y;
-                    } else {
-                        const R *B = sG + j * row + i;
-                        left = B[0];
-                        width = B[1] - left;
-                    }
+                    cell[j] = cell_address(grid0 + j * row_bytes, i);
+                    read_cell(cell[j], left, width);
                 }
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
@@ -713,12 +741,11 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 else
                     xj = rfma(cj[1], xu, cj[0]);
                 J = J * (width * cj[2]);
-                bin[j] = i;
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
                     r[j] = (double)u;
-                    r[D + j] = (double)i;
+                    r[D + j] = (double)((cell[j] - (grid0 + j * row_bytes)) >> 3);
                     r[2 * D + j] = (double)xj;
                 }
             }
@@ -738,7 +765,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) atomicAdd(&sH[j * nb + bin[j]], sq);
+                    if (j < axes) add_bin<D, F32>(cell[j], to_hist, j, sq);
             }
             if (traced) {
                 double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
