@@ -438,9 +438,9 @@ __device__ __forceinline__ uint32_t cell_address(uint32_t row_address, int i) {
 // A grid entry as it lies in LDS: the left boundary and the right one (FP64)
 // or the width (FP32); read_cell gives the width in both.
 __device__ __forceinline__ void load_cell(uint32_t cell, double &left, double &right) {
-    const LdsDouble *B = (const LdsDouble *)cell;
-    left = B[0];
-    right = B[1];
+    LdsDouble *B = (LdsDouble *)cell;
+    left = __hip_atomic_load(B, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    right = __hip_atomic_load(B + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 __device__ __forceinline__ void load_cell(uint32_t cell, float &left, float &width) {
     const uint64_t B = *(const LdsWord *)cell;  // one 8-byte read
