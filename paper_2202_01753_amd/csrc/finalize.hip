@@ -8,34 +8,26 @@
 
 namespace mcubes {
 
-hipError_t launch_sample_f0(int, int, int, size_t, hipStream_t, const SampleArgs &);
-hipError_t launch_sample_f1(int, int, int, size_t, hipStream_t, const SampleArgs &);
-hipError_t launch_sample_f2(int, int, int, size_t, hipStream_t, const SampleArgs &);
-hipError_t launch_sample_f3(int, int, int, size_t, hipStream_t, const SampleArgs &);
-const void *sample_kernel_f0(int, bool, bool);
-const void *sample_kernel_f1(int, bool, bool);
-const void *sample_kernel_f2(int, bool, bool);
-const void *sample_kernel_f3(int, bool, bool);
+const void *sample_kernel_f0(int, int, bool);
+const void *sample_kernel_f1(int, int, bool);
+const void *sample_kernel_f2(int, int, bool);
+const void *sample_kernel_f3(int, int, bool);
 
-const void *sample_kernel(int integrand, int dim, bool trace, bool fp32) {
+const void *sample_kernel(int integrand, int dim, int kind, bool fp32) {
     switch (integrand) {
-    case 0: return sample_kernel_f0(dim, trace, fp32);
-    case 1: return sample_kernel_f1(dim, trace, fp32);
-    case 2: return sample_kernel_f2(dim, trace, fp32);
-    case 3: return sample_kernel_f3(dim, trace, fp32);
+    case 0: return sample_kernel_f0(dim, kind, fp32);
+    case 1: return sample_kernel_f1(dim, kind, fp32);
+    case 2: return sample_kernel_f2(dim, kind, fp32);
+    case 3: return sample_kernel_f3(dim, kind, fp32);
     default: return nullptr;
     }
 }
 
-hipError_t launch_sample(int integrand, int dim, int blocks, int threads, size_t lds_bytes,
-                         hipStream_t stream, const SampleArgs &args) {
-    switch (integrand) {
-    case 0: return launch_sample_f0(dim, blocks, threads, lds_bytes, stream, args);
-    case 1: return launch_sample_f1(dim, blocks, threads, lds_bytes, stream, args);
-    case 2: return launch_sample_f2(dim, blocks, threads, lds_bytes, stream, args);
-    case 3: return launch_sample_f3(dim, blocks, threads, lds_bytes, stream, args);
-    default: return hipErrorInvalidValue;
-    }
+hipError_t launch_sample(const void *kernel, int blocks, int threads, size_t lds_bytes, hipStream_t stream,
+                         const SampleArgs &args) {
+    if (!kernel) return hipErrorInvalidValue;
+    void *params[] = {const_cast<SampleArgs *>(&args)};
+    return hipLaunchKernel(kernel, dim3(blocks), dim3(threads), params, lds_bytes, stream);
 }
 
 namespace {

@@ -8,6 +8,8 @@
 
 #include <cmath>
 #include <cstring>
+#include <map>
+#include <tuple>
 
 namespace mcubes {
 namespace host {
@@ -108,6 +110,46 @@ hipError_t allow_lds(const void *fn, size_t bytes) {
     hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (err != hipSuccess) return err;
     g_attr_set.emplace_back(fn, bytes);
+    return hipSuccess;
+}
+
+namespace {
+std::mutex g_occ_mu;
+std::map<std::tuple<int, const void *, int, size_t>, int> g_occ;  // device, kernel, threads, LDS
+std::map<int, int> g_cus;                                         // device
+}  // namespace
+
+hipError_t compute_units(int *cus) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(g_occ_mu);
+    auto it = g_cus.find(dev);
+    if (it == g_cus.end()) {
+        e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) g_cus.emplace(dev, *cus);
+        return e;
+    }
+    *cus = it->second;
+    return hipSuccess;
+}
+
+hipError_t occupancy(const void *fn, int threads, size_t lds_bytes, int *per_cu) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const auto key = std::make_tuple(dev, fn, threads, lds_bytes);
+    std::lock_guard<std::mutex> lock(g_occ_mu);
+    auto it = g_occ.find(key);
+    if (it == g_occ.end()) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, fn, threads, lds_bytes);
+        if (e == hipSuccess) {
+            if (g_occ.size() >= 4096) g_occ.clear();  // bounded: problems of any bin count ask
+            g_occ.emplace(key, *per_cu);
+        }
+        return e;
+    }
+    *per_cu = it->second;
     return hipSuccess;
 }
 
@@ -229,6 +271,7 @@ void sample_args(const mc_problem *pr, int64_t g, int64_t m, int64_t p, uint32_t
     a->p = (int32_t)p;
     a->nb = nb;
     a->g = (int32_t)g;
+    a->gmagic = g > 1 ? ~0ull / (uint64_t)g + 1 : 0;
     a->hist = adjust ? 1 : 0;
     a->kind = pr->integrand * 32 + pr->dim;
     a->one_d = pr->one_d ? 1 : 0;

@@ -54,6 +54,12 @@ size_t lds_bytes_of(int d, int nb, bool hist, bool fp32);
 mc_status validate(const mc_problem *pr);
 // Lets a kernel use more than 64 KB of dynamic LDS (once per kernel and size).
 hipError_t allow_lds(const void *fn, size_t bytes);
+// Compute units of the current device, and the workgroups of a kernel that one
+// of them holds at a time, at that workgroup size and dynamic LDS.  Both are
+// fixed by the device and the compiled kernel and kept for the process (a query
+// costs microseconds, a run asks a dozen).
+hipError_t compute_units(int *cus);
+hipError_t occupancy(const void *fn, int threads, size_t lds_bytes, int *per_cu);
 // Per-axis constants (kConstStride doubles per axis) in the layout the kernels read.
 std::vector<double> axis_constants(const mc_problem *pr);
 // The per-integral part of the sampling-kernel arguments (lattice, scales,

@@ -30,6 +30,7 @@ struct SampleArgs {
     int64_t t0, t1;         // traced sub-cube range
     int64_t stride;         // sub-cubes advanced per lane step (= grid size in threads)
     uint64_t seed;
+    uint64_t gmagic;        // ceil(2^64 / g) (0 for g = 1): quotients of 32-bit indices by g
     uint32_t iter;
     int32_t p;              // samples per sub-cube
     int32_t nb;             // bins per axis
@@ -38,7 +39,10 @@ struct SampleArgs {
     int32_t hist_stride;    // doubles between two histogram accumulators
     int32_t kind;           // integrand id * 32 + dim (dispatch in the batched kernel)
     int32_t one_d;          // nonzero: collect bin contributions of the first axis only
-    int32_t hist_copies;    // LDS histogram copies: 2 = lanes 32-63 of a wave add into a second
+    int32_t hist_copies;    // LDS histogram copies.  kPlain: 2 = lanes 32-63 of a wave add into a
+                            // second; kCopies, kSplit: 2^copy_shift, side by side per bin
+    int32_t copy_shift;
+    int32_t lsplit;         // kSplit: a sub-cube's samples go over 2^lsplit neighbouring lanes
     double s;               // nb / g
     float s32;              // nb / g rounded to float (FP32 evaluation)
     int32_t fp32;           // nonzero: FP32 evaluation
@@ -57,12 +61,18 @@ struct SampleArgs {
 //   [3] Gaussian centre or corner-peak coefficient   [4] Gaussian 1/width   [5] 0
 constexpr int kConstStride = 6;
 
-// Returns the sampling kernel for (integrand, dim, trace, FP32 evaluation), or nullptr.
-const void *sample_kernel(int integrand, int dim, bool trace, bool fp32);
+// The sampling kernels of one integrand, dimension and precision.
+constexpr int kPlain = 0;   // one lane per sub-cube
+constexpr int kTraced = 1;  // kPlain with per-sample and per-cube records
+constexpr int kCopies = 2;  // 2^copy_shift copies of every histogram bin side by side
+constexpr int kSplit = 3;   // kCopies, and a sub-cube's samples over 2^lsplit neighbouring lanes
 
-// Launches the sampling kernel; lds_bytes is the dynamic LDS size.
-hipError_t launch_sample(int integrand, int dim, int blocks, int threads, size_t lds_bytes,
-                         hipStream_t stream, const SampleArgs &args);
+// The sampling kernel of that kind, or nullptr.
+const void *sample_kernel(int integrand, int dim, int kind, bool fp32);
+
+// Launches a sampling kernel; lds_bytes is the dynamic LDS size.
+hipError_t launch_sample(const void *kernel, int blocks, int threads, size_t lds_bytes, hipStream_t stream,
+                         const SampleArgs &args);
 
 // Histogram accumulators of a V-Sample pass (a region of their own, so that
 // the totals of a pass with more workgroups never reach them): workgroup b

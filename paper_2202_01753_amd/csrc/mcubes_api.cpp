@@ -30,22 +30,31 @@ namespace {
 
 // ------------------------------------------------------------------ launch geometry and workspace
 
-struct Geometry {
-    int64_t g, m, p;
+// A sampling launch: which kernel, its shape in adjusting and No-Adjust passes.
+struct Launch {
+    int kind;                 // kPlain, kTraced, kCopies or kSplit
+    const void *fn;
     int threads;
     int blocks_adj, blocks_noadj;
     size_t lds_adj, lds_noadj;
+    int hist_copies;          // LDS histogram copies in adjusting passes
+    int copy_shift, lsplit;   // kCopies, kSplit: log2 of the copies, of the lanes per sub-cube
+    int blocks(bool adjust) const { return adjust ? blocks_adj : blocks_noadj; }
+    size_t lds(bool adjust) const { return adjust ? lds_adj : lds_noadj; }
+};
+
+struct Geometry {
+    int64_t g, m, p;
+    Launch run, traced;       // of untraced and of traced passes
     int hist_stride;          // doubles per histogram accumulator (padded)
-    int hist_copies;          // LDS histogram copies in adjusting passes (1 or 2)
     size_t off_consts, off_grid, off_tables, off_partials, off_hist, off_out, off_flag, off_run, total;
 };
 
 mc_status blocks_for(const void *fn, int threads, size_t lds, int64_t m, int requested, int *out) {
-    int dev = 0, cus = 0, per_cu = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    int cus = 0, per_cu = 0;
+    HIP_TRY(compute_units(&cus));
     HIP_TRY(allow_lds(fn, lds));
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds));
+    HIP_TRY(occupancy(fn, threads, lds, &per_cu));
     if (per_cu < 1) return MC_EINVAL;
     // Where several workgroups share a CU, launch more than fit at once: the
     // workgroups are smaller, and CUs that were handed fewer of them take more
@@ -80,7 +89,7 @@ mc_status pick_threads(const void *fn, size_t lds, int *out) {
     int best = 0, best_waves = -1;
     for (int t : {1024, 768, 512, 256}) {
         int per_cu = 0;
-        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, t, lds));
+        HIP_TRY(occupancy(fn, t, lds, &per_cu));
         const int waves = per_cu * t / 64;
         if (waves > best_waves) {
             best_waves = waves;
@@ -92,6 +101,139 @@ mc_status pick_threads(const void *fn, size_t lds, int *out) {
     return MC_OK;
 }
 
+// The launch of one lane per sub-cube (kPlain; kTraced in its shape).
+mc_status plain_launch(const mc_problem *pr, int64_t m, Launch *out) {
+    const int d = pr->dim, nb = pr->nbins;
+    const bool f32 = is_fp32(pr);
+    Launch L{};
+    L.kind = kPlain;
+    L.fn = sample_kernel(pr->integrand, d, kPlain, f32);
+    if (!L.fn) return MC_EINVAL;
+    L.lds_adj = lds_bytes_of(d, nb, true, f32);
+    L.lds_noadj = lds_bytes_of(d, nb, false, f32);
+    mc_status st;
+    if (pr->threads) {
+        L.threads = pr->threads;
+    } else {
+        st = pick_threads(L.fn, L.lds_adj, &L.threads);
+        if (st != MC_OK) return st;
+    }
+    // A second LDS copy of the histogram, for the upper half of each wave,
+    // halves the lanes that add into one bin at once (lanes of a wave share
+    // the strata of all but the fastest axes, so many fall into the same few
+    // bins); taken where the extra LDS keeps as many workgroups resident.
+    L.hist_copies = 1;
+    const size_t lds2 = L.lds_adj + sizeof(double) * d * (size_t)nb;
+    if (lds2 <= kLdsDynamicLimit) {
+        int per1 = 0, per2 = 0;
+        HIP_TRY(allow_lds(L.fn, lds2));
+        HIP_TRY(occupancy(L.fn, L.threads, L.lds_adj, &per1));
+        HIP_TRY(occupancy(L.fn, L.threads, lds2, &per2));
+        if (per2 >= per1 && per2 > 0) {
+            L.hist_copies = 2;
+            L.lds_adj = lds2;
+        }
+    }
+    st = blocks_for(L.fn, L.threads, L.lds_adj, m, pr->blocks, &L.blocks_adj);
+    if (st != MC_OK) return st;
+    st = blocks_for(L.fn, L.threads, L.lds_noadj, m, pr->blocks, &L.blocks_noadj);
+    if (st != MC_OK) return st;
+    *out = L;
+    return MC_OK;
+}
+
+// What a launch with this many waves per CU and histogram copies (1: kPlain,
+// with its second copy for half the lanes or not) is worth against others of
+// the same problem.  Below 24 waves the kernels cover less of their latency;
+// copies side by side take lanes that meet in one bin, or on one LDS bank,
+// apart (an FP64 LDS atomic takes 8.7 cycles per wave with 64 different
+// banks, 26 at random bins of 500, 33 at random bins of 42, 192 in one bin).
+// Measured against kPlain: 4 copies at equal waves 1.04-2.5 times as fast
+// (d = 2 to 10, 100 to 500 bins, 1e6 to 1e8 samples), 8 or 16 copies at 16
+// waves against 24 1.05-1.39; 4 copies at 16 against 24 0.92-0.96 in FP64 and with
+// the tables, whose VALU work leaves the LDS idle at times, and 1.09-1.11 in
+// FP32 evaluation of the closed forms, where the LDS sets the pace.
+double launch_worth(int waves, int copies, bool lds_bound) {
+    const double w = waves >= 24 ? 1.0 : waves >= 20 ? 0.96 : waves >= 16 ? 0.90 : waves / 16.0 * 0.90;
+    const double c = copies >= 16 ? 1.05 : copies >= 8 ? 1.03 : copies >= 4 ? (lds_bound ? 1.0 : 0.95) : 0.87;
+    return w * c;
+}
+
+// The launch with several copies of the histogram side by side (kCopies) and,
+// where there are fewer sub-cubes than lanes, a sub-cube's samples over
+// several lanes (kSplit), where it is worth more than the plain one, which
+// *out holds on entry.
+mc_status copies_launch(const mc_problem *pr, int64_t m, int64_t p, const Launch &plain, Launch *out) {
+    const int d = pr->dim, nb = pr->nbins;
+    const bool f32 = is_fp32(pr);
+    const size_t grid = lds_bytes_of(d, nb, false, f32), one = sizeof(double) * d * (size_t)nb;
+    const bool lds_bound = f32 && pr->integrand != MC_F_GAUSS_TABLES;
+    int cus = 0, per_cu = 0;
+    HIP_TRY(compute_units(&cus));
+    HIP_TRY(occupancy(plain.fn, plain.threads, plain.lds_adj, &per_cu));
+    const double plain_worth = launch_worth(per_cu * plain.threads / 64, 1, lds_bound);
+    Launch L{};
+    L.kind = kCopies;
+    L.fn = sample_kernel(pr->integrand, d, kCopies, f32);
+    if (!L.fn) return MC_EINVAL;
+    double best = 0.0;
+    for (int t : {1024, 768, 512, 256}) {
+        if (pr->threads && t != 1024) break;
+        const int threads = pr->threads ? pr->threads : t;
+        for (int cs = 4; cs >= 2; --cs) {
+            const size_t lds = grid + (one << cs);
+            if (lds > kLdsDynamicLimit) continue;
+            HIP_TRY(allow_lds(L.fn, lds));
+            HIP_TRY(occupancy(L.fn, threads, lds, &per_cu));
+            const double worth = launch_worth(per_cu * threads / 64, 1 << cs, lds_bound);
+            if (per_cu > 0 && worth > best) {
+                best = worth;
+                L.threads = threads;
+                L.copy_shift = cs;
+            }
+        }
+    }
+    if (best <= plain_worth) return MC_OK;
+    // Lanes: the resident ones.  Fewer sub-cubes than that: as many lanes per
+    // sub-cube as still fit, each with a sample or more to do, and smaller
+    // workgroups where the lanes would otherwise fill only some of the CUs
+    // (ten axes, 1e6 samples, 59049 sub-cubes of 16 samples: 84 -> 40 us per pass;
+    // eight axes, 1e5 samples, 6561 of 15: 47 -> 25 us).
+    HIP_TRY(occupancy(L.fn, L.threads, grid + (one << L.copy_shift), &per_cu));
+    int64_t resident = (int64_t)per_cu * cus;
+    if (pr->blocks) resident = pr->blocks;
+    while (L.lsplit < 6 && (2 << L.lsplit) <= p && m <= (resident * L.threads) >> (L.lsplit + 1)) ++L.lsplit;
+    const int64_t lanes = m << L.lsplit;
+    if (!pr->threads) {
+        if (lanes <= (int64_t)cus * 256) L.threads = 256;
+        else if (lanes <= (int64_t)cus * 512) L.threads = std::min(L.threads, 512);
+    }
+    if (L.lsplit) {
+        L.kind = kSplit;
+        L.fn = sample_kernel(pr->integrand, d, kSplit, f32);
+        if (!L.fn) return MC_EINVAL;
+    }
+    const int64_t useful = (lanes + L.threads - 1) / L.threads;
+    // clearing and adding up the copies is work per workgroup: no more of them
+    // than twice the samples a bin of the workgroup gets
+    const int64_t per_wg = m * p / std::max<int64_t>(1, std::min(useful, resident));
+    while (L.copy_shift > 0 && ((int64_t)nb << L.copy_shift) > 2 * per_wg) --L.copy_shift;
+    L.hist_copies = 1 << L.copy_shift;
+    L.lds_noadj = grid;
+    L.lds_adj = grid + (one << L.copy_shift);
+    for (int adj = 0; adj < 2; ++adj) {
+        const size_t lds = adj ? L.lds_adj : L.lds_noadj;
+        HIP_TRY(allow_lds(L.fn, lds));
+        HIP_TRY(occupancy(L.fn, L.threads, lds, &per_cu));
+        if (per_cu < 1) return MC_OK;
+        int64_t blocks = pr->blocks ? pr->blocks : std::min((int64_t)per_cu * cus, useful);
+        blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, 1 << 20));
+        (adj ? L.blocks_adj : L.blocks_noadj) = (int)blocks;
+    }
+    *out = L;
+    return MC_OK;
+}
+
 mc_status geometry(const mc_problem *pr, Geometry *geo) {
     mc_status st = validate(pr);
     if (st != MC_OK) return st;
@@ -99,41 +241,17 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     lattice(pr->dim, pr->maxcalls, &G.g, &G.m, &G.p);
     const int d = pr->dim, nb = pr->nbins;
     const bool f32 = is_fp32(pr);
-    G.lds_adj = lds_bytes_of(d, nb, true, f32);
-    G.lds_noadj = lds_bytes_of(d, nb, false, f32);
-    const void *fn = sample_kernel(pr->integrand, d, false, f32);
-    if (!fn) return MC_EINVAL;
-    if (pr->threads) {
-        G.threads = pr->threads;
-    } else {
-        st = pick_threads(fn, G.lds_adj, &G.threads);
-        if (st != MC_OK) return st;
-    }
-    // A second LDS copy of the histogram, for the upper half of each wave,
-    // halves the lanes that add into one bin at once (lanes of a wave share
-    // the strata of all but the fastest axes, so many fall into the same few
-    // bins); taken where the extra LDS keeps as many workgroups resident.
-    G.hist_copies = 1;
-    {
-        const size_t lds2 = G.lds_adj + sizeof(double) * d * (size_t)nb;
-        if (lds2 <= kLdsDynamicLimit) {
-            int per1 = 0, per2 = 0;
-            HIP_TRY(allow_lds(fn, lds2));
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per1, fn, G.threads, G.lds_adj));
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per2, fn, G.threads, lds2));
-            if (per2 >= per1 && per2 > 0) {
-                G.hist_copies = 2;
-                G.lds_adj = lds2;
-            }
-        }
-    }
-    st = blocks_for(fn, G.threads, G.lds_adj, G.m, pr->blocks, &G.blocks_adj);
+    Launch plain{};
+    st = plain_launch(pr, G.m, &plain);
     if (st != MC_OK) return st;
-    st = blocks_for(fn, G.threads, G.lds_noadj, G.m, pr->blocks, &G.blocks_noadj);
+    G.run = G.traced = plain;
+    G.traced.kind = kTraced;
+    G.traced.fn = sample_kernel(pr->integrand, d, kTraced, f32);
+    st = copies_launch(pr, G.m, G.p, plain, &G.run);
     if (st != MC_OK) return st;
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
-    const size_t part_adj = 4 * (size_t)G.blocks_adj;
-    const size_t part_noadj = 4 * (size_t)G.blocks_noadj;
+    const size_t most_blocks = (size_t)std::max(std::max(G.run.blocks_adj, G.run.blocks_noadj),
+                                                std::max(G.traced.blocks_adj, G.traced.blocks_noadj));
     size_t off = 0;
     const size_t real = f32 ? sizeof(float) : sizeof(double);
     G.off_consts = off;
@@ -143,7 +261,7 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     G.off_tables = off;
     if (pr->integrand == MC_F_GAUSS_TABLES) off = align_up(off + real * (f32 ? kTablesLen32 : kTablesLen));
     G.off_partials = off;
-    off = align_up(off + sizeof(double) * std::max(part_adj, part_noadj));
+    off = align_up(off + sizeof(double) * 4 * most_blocks);
     // the kHistAcc histogram accumulators of adjusting passes, kept zero
     // between passes
     G.off_hist = off;
@@ -162,17 +280,19 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
 
 // ------------------------------------------------------------------ one sampling pass
 
-void fill_args(const mc_problem *pr, const Geometry &G, char *ws, uint32_t iter, bool adjust,
-               int blocks, SampleArgs *a) {
+void fill_args(const mc_problem *pr, const Geometry &G, const Launch &L, char *ws, uint32_t iter, bool adjust,
+               SampleArgs *a) {
     const double *grid = reinterpret_cast<const double *>(ws + G.off_grid);
     const void *tables = pr->integrand == MC_F_GAUSS_TABLES ? ws + G.off_tables : nullptr;
     sample_args(pr, G.g, G.m, G.p, iter, adjust, ws + G.off_consts, grid, tables, a);
     a->partials = reinterpret_cast<double *>(ws + G.off_partials);
     a->hist_acc = reinterpret_cast<double *>(ws + G.off_hist);
     a->flag = reinterpret_cast<uint32_t *>(ws + G.off_flag);
-    a->stride = (int64_t)blocks * G.threads;
+    a->stride = ((int64_t)L.blocks(adjust) * L.threads) >> L.lsplit;
     a->hist_stride = G.hist_stride;
-    a->hist_copies = adjust ? G.hist_copies : 1;
+    a->hist_copies = adjust ? L.hist_copies : 1;
+    a->copy_shift = adjust ? L.copy_shift : 0;
+    a->lsplit = L.lsplit;
     // the per-lane stride in base g (only d digits are used: a lane that
     // overflows the top digit has left the lattice)
     int64_t rest = a->stride;
@@ -231,10 +351,11 @@ mc_status run_pass(const mc_problem *pr, const Geometry &G, char *ws, hipStream_
                    double *trace, int64_t t0, int64_t t1, Events *ev, double *ms_sample,
                    double *ms_fin, int spin_us = 0, bool pinned = true) {
     const int d = pr->dim, nb = pr->nbins;
-    const int blocks = adjust ? G.blocks_adj : G.blocks_noadj;
-    const size_t lds = adjust ? G.lds_adj : G.lds_noadj;
+    const Launch &L = trace ? G.traced : G.run;
+    const int blocks = L.blocks(adjust);
+    const size_t lds = L.lds(adjust);
     SampleArgs a;
-    fill_args(pr, G, ws, iter, adjust, blocks, &a);
+    fill_args(pr, G, L, ws, iter, adjust, &a);
     a.trace = trace;
     a.t0 = t0;
     a.t1 = t1;
@@ -250,8 +371,8 @@ mc_status run_pass(const mc_problem *pr, const Geometry &G, char *ws, hipStream_
     HIP_TRY(hipMemcpyAsync(ws + G.off_grid, pinned ? stage : static_cast<const void *>(h_grid),
                            grid_bytes, hipMemcpyHostToDevice, stream));
     if (ev) HIP_TRY(hipEventRecord(ev->e[0], stream));
-    HIP_TRY(allow_lds(sample_kernel(pr->integrand, d, trace != nullptr, is_fp32(pr)), lds));
-    HIP_TRY(launch_sample(pr->integrand, d, blocks, G.threads, lds, stream, a));
+    HIP_TRY(allow_lds(L.fn, lds));
+    HIP_TRY(launch_sample(L.fn, blocks, L.threads, lds, stream, a));
     if (ev) HIP_TRY(hipEventRecord(ev->e[1], stream));
     double *out_dev = reinterpret_cast<double *>(ws + G.off_out);
     HIP_TRY(launch_finalize(a.partials, a.hist_acc, blocks, d * nb, G.hist_stride, adjust ? 1 : 0, a.flag,
@@ -345,9 +466,9 @@ mc_status mc_launch_shape(const mc_problem *prob, int32_t adjust, int32_t *block
     Geometry G;
     mc_status st = geometry(prob, &G);
     if (st != MC_OK) return st;
-    *blocks = adjust ? G.blocks_adj : G.blocks_noadj;
-    *threads = G.threads;
-    *lds_bytes = (int32_t)(adjust ? G.lds_adj : G.lds_noadj);
+    *blocks = G.run.blocks(adjust != 0);
+    *threads = G.run.threads;
+    *lds_bytes = (int32_t)G.run.lds(adjust != 0);
     return MC_OK;
 }
 
@@ -517,20 +638,19 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
     double *hist_acc = reinterpret_cast<double *>(ws + G.off_hist);
     uint32_t *flag = reinterpret_cast<uint32_t *>(ws + G.off_flag);
     hipEvent_t *done = timing ? ev->done : nullptr;
-    const void *fn = sample_kernel(prob->integrand, d, false, is_fp32(prob));
-    auto pass_blocks = [&](int it) { return it < prob->ita ? G.blocks_adj : G.blocks_noadj; };
+    const Launch &L = G.run;
+    auto pass_blocks = [&](int it) { return L.blocks(it < prob->ita); };
     // the sampling kernel of pass it (and its marker)
     auto head = [&](int it) -> hipError_t {
         const bool adjust = it < prob->ita;
-        const size_t lds = adjust ? G.lds_adj : G.lds_noadj;
+        const size_t lds = L.lds(adjust);
         SampleArgs a;
-        fill_args(prob, G, ws, (uint32_t)it, adjust, pass_blocks(it), &a);
+        fill_args(prob, G, L, ws, (uint32_t)it, adjust, &a);
         a.run_last = &dst->last;
         hipError_t e;
         if (timing && it == 0 && (e = hipEventRecord(ev->start, s)) != hipSuccess) return e;
-        if ((e = allow_lds(fn, lds)) != hipSuccess) return e;
-        if ((e = launch_sample(prob->integrand, d, pass_blocks(it), G.threads, lds, s, a)) != hipSuccess)
-            return e;
+        if ((e = allow_lds(L.fn, lds)) != hipSuccess) return e;
+        if ((e = launch_sample(L.fn, pass_blocks(it), L.threads, lds, s, a)) != hipSuccess) return e;
         return timing ? hipEventRecord(ev->sampled[it % 3], s) : hipSuccess;
     };
     // the rest of pass it: totals, decision and bin adjustment in one launch,
@@ -620,9 +740,9 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
         timing->sample_ms = ms_s;
         timing->finalize_ms = ms_f;
         timing->launches = k;
-        timing->blocks = prob->ita > 0 ? G.blocks_adj : G.blocks_noadj;
-        timing->threads = G.threads;
-        timing->lds_bytes = (int32_t)(prob->ita > 0 ? G.lds_adj : G.lds_noadj);
+        timing->blocks = G.run.blocks(prob->ita > 0);
+        timing->threads = G.run.threads;
+        timing->lds_bytes = (int32_t)G.run.lds(prob->ita > 0);
     }
     return MC_OK;
 }
@@ -700,9 +820,9 @@ mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *s
         timing->sample_ms = ms_s;
         timing->finalize_ms = ms_f;
         timing->launches = k;
-        timing->blocks = prob->ita > 0 ? G.blocks_adj : G.blocks_noadj;
-        timing->threads = G.threads;
-        timing->lds_bytes = (int32_t)(prob->ita > 0 ? G.lds_adj : G.lds_noadj);
+        timing->blocks = G.run.blocks(prob->ita > 0);
+        timing->threads = G.run.threads;
+        timing->lds_bytes = (int32_t)G.run.lds(prob->ita > 0);
     }
     return MC_OK;
 }

@@ -453,9 +453,10 @@ __device__ __forceinline__ void read_cell(uint32_t cell, R &left, R &width) {
     if constexpr (!std::is_same<R, float>::value) width = width - left;
 }
 
-template <int D, bool F32>
+// (COPIES: cell is the bin's entry in row 0, to_hist the row's distance.)
+template <int D, bool F32, bool COPIES>
 __device__ __forceinline__ void add_bin(uint32_t cell, uint32_t to_hist, int j, double v) {
-    LdsDouble *h = (LdsDouble *)(cell + to_hist) + (F32 ? 0 : D - 1 - j);
+    LdsDouble *h = (LdsDouble *)(cell + to_hist) + (F32 || COPIES ? 0 : D - 1 - j);
     __hip_atomic_fetch_add(h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -533,9 +534,9 @@ constexpr bool kLowInVgpr = F32 ? (F == 3 && D == 6) : ((F == 1 || F == 3) && D 
 // kernel at d = 6 (two 72 KB workgroups of 768 threads per CU): 0.6% faster;
 // the d = 8 corner-peak kernels, also at 6 by their LDS, measured 0.5-1.5%
 // slower with it.
-template <int F, int D, bool TRACE, bool F32>
+template <int F, int D, int KIND, bool F32>
 constexpr int kFixedWaves =
-    TRACE ? 0
+    KIND != kPlain && KIND != kCopies ? 0
           : (!F32 && ((F == 1 && D >= 6 && D <= 8) || (F == 3 && (D == 6 || D == 7)))) ? 4
           : (F32 && F == 3 && D == 6) ? 6
                                       : 0;
@@ -552,7 +553,7 @@ constexpr int kFixedWaves =
 // the one-sample path raises the wave's priority for the first part of each
 // sample (the pair path always does).
 template <int F, int D, bool TRACE, bool F32, bool PAIR, bool EARLY, bool LOV = false, bool GF = false,
-          bool PRIO = false, typename A, typename CP>
+          bool PRIO = false, bool COPIES = false, bool SPLIT = false, typename A, typename CP>
 __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP sC, uint64_t t,
                                           const uint32_t (&dig)[D], double &It, double &vt,
                                           bool &bad, const real_t<F32> *lov = nullptr) {
@@ -570,7 +571,17 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     // histogram copies the upper half of each wave adds into the second, so at
     // most half as many lanes add into one bin at once
     uint32_t to_hist = lds_address(v.hist) - grid0 - (F32 ? 0u : 8u * (D - 1));
-    if (a.hist_copies > 1 && (threadIdx.x & 32)) to_hist += (uint32_t)(D * nb) * 8u;
+    if (!COPIES && a.hist_copies > 1 && (threadIdx.x & 32)) to_hist += (uint32_t)(D * nb) * 8u;
+    // COPIES: the copies of a bin lie next to each other (row, bin, copy), and a
+    // lane adds into copy lane mod copies
+    const uint32_t copy_sh = COPIES ? 3u + (uint32_t)a.copy_shift : 3u;
+    const uint32_t lane_hist =
+        COPIES ? lds_address(v.hist) + ((threadIdx.x & ((1u << a.copy_shift) - 1u)) << 3) : 0u;
+    const uint32_t hist_row = (uint32_t)nb << copy_sh;
+    // SPLIT: lane q of a group of 2^lsplit neighbours takes the samples q, q +
+    // 2^lsplit, ... of the group's sub-cube
+    const int kstep = SPLIT ? 1 << a.lsplit : 1;
+    const int kfirst = SPLIT ? (int)(threadIdx.x & (uint32_t)(kstep - 1)) : 0;
 
     R cd[D];
 #pragma unroll
@@ -581,8 +592,9 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
 
     double I0 = 0.0, S1 = 0.0, S2 = 0.0;
     if constexpr (PAIR) {
-        // One sample: its value I_k and its grid cell on every axis (and its trace record).
-        auto point = [&](int k, uint32_t (&cell)[D]) -> double {
+        // One sample: its value I_k and, per axis, the grid cell or histogram
+        // entry that add_bin takes (and its trace record).
+        auto point = [&](int k, uint32_t (&target)[D]) -> double {
             // raised wave priority while the sample's random words, bins and
             // grid reads are formed, back to normal before its integrand
             // value (see the one-sample path below; FP32-eval Gaussian and
@@ -602,9 +614,10 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const R z = (cd[j] + u) * s;
                 int i;
                 const R frac = bin_of(z, last, lastr, i);
-                cell[j] = cell_address(grid0 + j * row_bytes, i);
+                const uint32_t cell = cell_address(grid0 + j * row_bytes, i);
+                target[j] = COPIES ? ((uint32_t)i << copy_sh) + lane_hist : cell;
                 R left, width;
-                read_cell(cell[j], left, width);
+                read_cell(cell, left, width);
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
                 R xj;
@@ -636,7 +649,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
         // shifted sums in sample order
         // (for k == 0 the deviation is exactly +0 and leaves S1 = S2 = +0)
         auto accumulate = [&](int k, double Ik) {
-            if (k == 0) I0 = Ik;
+            if (k == kfirst) I0 = Ik;
             const double dev = Ik - I0;
             S1 = S1 + dev;
             S2 = __fma_rn(dev, dev, S2);
@@ -647,19 +660,19 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) add_bin<D, F32>(cell[j], to_hist, j, sq);
+                    if (j < axes) add_bin<D, F32, COPIES>(cell[j], COPIES ? j * hist_row : to_hist, j, sq);
             }
         };
         {
             // both points (grid reads included) before either sample's histogram
             // atomics, so that the two evaluations can interleave
-            int k = 0;
-            for (; k + 1 < a.p; k += 2) {
+            int k = kfirst;
+            for (; k + kstep < a.p; k += 2 * kstep) {
                 uint32_t cell0[D], cell1[D];
                 const double Ia = point(k, cell0);
-                const double Ib = point(k + 1, cell1);
+                const double Ib = point(k + kstep, cell1);
                 accumulate(k, Ia);
-                accumulate(k + 1, Ib);
+                accumulate(k + kstep, Ib);
                 add_bins(cell0, Ia);
                 add_bins(cell1, Ib);
             }
@@ -674,7 +687,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
         // the same steps one sample at a time, written out in the loop: the
         // batched kernel, which inlines every case, allocates fewer registers
         // for this form than for the lambda one
-        for (int k = 0; k < a.p; ++k) {
+        for (int k = kfirst; k < a.p; k += kstep) {
             // PRIO: the wave runs at raised priority from the start of a
             // sample until its integrand value.  s_setprio only orders issue
             // among the waves of a SIMD; favouring the waves that are still on
@@ -691,7 +704,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             for (int b = 0; b < NUSED; ++b)
                 philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
-            uint32_t cell[D];
+            uint32_t cell[D];  // grid cells, or (COPIES) histogram entries
             R J = R(1);
             // GF: every axis's bin and grid read first, then the rest axis by
             // axis, so that the grid reads are in flight together rather
@@ -708,6 +721,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     gf_frac[j] = bin_of(z, last, lastr, i);
                     cell[j] = cell_address(grid0 + j * row_bytes, i);
                     load_cell(cell[j], gf_left[j], gf_right[j]);
+                    if constexpr (COPIES) cell[j] = ((uint32_t)i << copy_sh) + lane_hist;
                 }
                 __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of their uses
                 if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
@@ -732,6 +746,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     frac = bin_of(z, last, lastr, i);
                     cell[j] = cell_address(grid0 + j * row_bytes, i);
                     read_cell(cell[j], left, width);
+                    if constexpr (COPIES) cell[j] = ((uint32_t)i << copy_sh) + lane_hist;
                 }
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
@@ -754,9 +769,9 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             const double Fv = (double)f * (double)J;
             bad |= !isfinite(Fv);
             const double Ik = Fv * a.inv;
-            if (k == 0) I0 = Ik;
+            if (k == kfirst) I0 = Ik;
             {
-                const double dev = Ik - I0;  // exactly +0 for k == 0: S1, S2 stay +0
+                const double dev = Ik - I0;  // exactly +0 for the first: S1, S2 stay +0
                 S1 = S1 + dev;
                 S2 = __fma_rn(dev, dev, S2);
             }
@@ -765,7 +780,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) add_bin<D, F32>(cell[j], to_hist, j, sq);
+                    if (j < axes) add_bin<D, F32, COPIES>(cell[j], COPIES ? j * hist_row : to_hist, j, sq);
             }
             if (traced) {
                 double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -774,10 +789,28 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             }
         }
     }
+    if constexpr (SPLIT) {
+        if (kstep > 1) {
+            // the group's sums: each lane's, shifted from its own first value to
+            // the sub-cube's (that of the group's first lane), then a butterfly
+            const int lane = threadIdx.x & 63;
+            const double c0 = __shfl(I0, lane & ~(kstep - 1), 64);
+            const double n = (double)((a.p - kfirst + kstep - 1) >> a.lsplit);
+            const double dd = I0 - c0;
+            S2 = __fma_rn(n * dd, dd, __fma_rn(2.0 * dd, S1, S2));
+            S1 = __fma_rn(n, dd, S1);
+            for (int off = kstep >> 1; off >= 1; off >>= 1) {
+                S1 = S1 + __shfl_xor(S1, off, 64);
+                S2 = S2 + __shfl_xor(S2, off, 64);
+            }
+            I0 = c0;
+        }
+    }
     It = __fma_rn(a.pd, I0, S1);
     const double num = __fma_rn(-S1, S1, a.pd * S2);
     vt = num * a.inv_pm1;
     if (vt < 0.0) vt = 0.0;
+    if (SPLIT && kfirst != 0) It = vt = 0.0;  // the group's first lane counts the sub-cube
     if (traced) {
         double *r = a.trace + (uint64_t)(a.t1 - a.t0) * (uint64_t)a.p * rec + (t - a.t0) * 2;
         r[0] = It;
@@ -795,6 +828,22 @@ __device__ __forceinline__ void odometer_add(uint32_t (&dig)[D], const int32_t *
         const uint32_t v = dig[j] + (uint32_t)step[j] + carry;  // < 2g + 1 <= 2^31 + 1
         carry = v >= g ? 1u : 0u;
         dig[j] = carry ? v - g : v;
+    }
+}
+
+// The digits of t in base g.  Below 2^32 each division is a product with
+// gmagic = ceil(2^64 / g), whose upper word is the exact quotient for 32-bit t
+// (two multiply-adds, where a 64-bit division takes about a hundred
+// instructions: for ten digits that was longer than sampling a sub-cube).
+template <int D>
+__device__ __forceinline__ void digits_of32(uint32_t t, uint32_t g, uint64_t gmagic, uint32_t (&dig)[D]) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        const uint64_t lo = (uint64_t)(uint32_t)gmagic * t;
+        const uint64_t hi = (uint64_t)(uint32_t)(gmagic >> 32) * t + (lo >> 32);
+        const uint32_t q = (uint32_t)(hi >> 32);
+        dig[j] = t - q * g;
+        t = q;
     }
 }
 
@@ -852,14 +901,17 @@ __device__ __forceinline__ void block_totals(double sI, double cI, double sV, do
 // ---------------------------------------------------------------- the kernel
 
 // One integral: persistent workgroups stride through all m sub-cubes.
-// TRACE instantiations additionally write per-sample and per-cube records for
-// the sub-cubes [t0, t1); F32 instantiations evaluate the map and the
+// kTraced instantiations additionally write per-sample and per-cube records for
+// the sub-cubes [t0, t1); kSplit ones spread the samples of a sub-cube over
+// 2^lsplit neighbouring lanes and keep copies of every bin side by side; F32 instantiations evaluate the map and the
 // integrand in single precision.  Everything from I_k on is FP64 in both.
-template <int F, int D, bool TRACE, bool F32>
+template <int F, int D, int KIND, bool F32>
 __global__ void __launch_bounds__(kMaxBlock)
-    __attribute__((amdgpu_waves_per_eu(kFixedWaves<F, D, TRACE, F32> ? kFixedWaves<F, D, TRACE, F32> : 1,
-                                       kFixedWaves<F, D, TRACE, F32> ? kFixedWaves<F, D, TRACE, F32> : 8)))
+    __attribute__((amdgpu_waves_per_eu(kFixedWaves<F, D, KIND, F32> ? kFixedWaves<F, D, KIND, F32> : 1,
+                                       kFixedWaves<F, D, KIND, F32> ? kFixedWaves<F, D, KIND, F32> : 8)))
     vsample_kernel(const SampleArgs a) {
+    constexpr bool TRACE = KIND == kTraced, SPLIT = KIND == kSplit, COPIES = SPLIT || KIND == kCopies;
+    constexpr bool LOV = !SPLIT && kLowInVgpr<F, D, F32>;
     if (a.run_last && (int64_t)a.iter > (int64_t)*a.run_last) return;  // the run has ended
     extern __shared__ double lds[];
     const LdsView<F32> v(lds, D, a.nb);
@@ -873,15 +925,16 @@ __global__ void __launch_bounds__(kMaxBlock)
     // read-back per use.
     volatile Const<real_t<F32>> *sC = (volatile Const<real_t<F32>> *)a.consts;
 
-    uint64_t t = (uint64_t)blockIdx.x * (uint64_t)blockDim.x + (uint64_t)threadIdx.x;
+    // this lane's first sub-cube (below 2^32: at most 2^20 workgroups)
+    uint64_t t = ((uint64_t)blockIdx.x * (uint64_t)blockDim.x + (uint64_t)threadIdx.x) >> (SPLIT ? a.lsplit : 0);
     uint32_t dig[D];
-    digits_of<D>(t, (uint32_t)a.g, dig);
+    digits_of32<D>((uint32_t)t, (uint32_t)a.g, a.gmagic, dig);
     double sI = 0.0, cI = 0.0, sV = 0.0, cV = 0.0;
     bool bad = false;
     // the lower bounds, copied once into vector registers (the empty asm keeps
     // the copies there rather than reloading them as scalars)
     real_t<F32> lov[D];
-    if constexpr (kLowInVgpr<F, D, F32>) {
+    if constexpr (LOV) {
 #pragma unroll
         for (int j = 0; j < D; ++j) {
             lov[j] = sC[kConstStride * j];
@@ -890,9 +943,8 @@ __global__ void __launch_bounds__(kMaxBlock)
     }
     while (t < (uint64_t)a.m) {
         double It, vt;
-        cube_pass<F, D, TRACE, F32, kPairSamples<F, D, F32>, true, kLowInVgpr<F, D, F32>,
-                  kGridFirst<F, D, F32>, kGridFirst<F, D, F32>>(
-            a, v, sC, t, dig, It, vt, bad, lov);
+        cube_pass<F, D, TRACE, F32, kPairSamples<F, D, F32>, true, LOV, kGridFirst<F, D, F32>,
+                  kGridFirst<F, D, F32>, COPIES, SPLIT>(a, v, sC, t, dig, It, vt, bad, lov);
         two_sum_add(sI, cI, It);
         two_sum_add(sV, cV, vt);
         // next sub-cube of this lane: t += stride, digit by digit
@@ -906,28 +958,38 @@ __global__ void __launch_bounds__(kMaxBlock)
         const int n = D * a.nb;
         double *acc = a.hist_acc + (size_t)(blockIdx.x % kHistAcc) * a.hist_stride;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const double h = a.hist_copies > 1 ? v.hist[i] + v.hist[n + i] : v.hist[i];
+            double h;
+            if constexpr (COPIES) {
+                // the copies from a different one on in neighbouring lanes, so
+                // that they read different banks
+                h = 0.0;
+                for (int c = 0; c < a.hist_copies; ++c)
+                    h += v.hist[i * a.hist_copies + ((c + (int)threadIdx.x) & (a.hist_copies - 1))];
+            } else {
+                h = a.hist_copies > 1 ? v.hist[i] + v.hist[n + i] : v.hist[i];
+            }
             if (h != 0.0) unsafeAtomicAdd(acc + i, h);
         }
     }
 }
 
+// The kernels of one integrand and dimension, as launch_sample takes them.
 template <int F, int D>
-hipError_t launch_sample_fd(int blocks, int threads, size_t lds_bytes, hipStream_t stream,
-                            const SampleArgs &args) {
-    const dim3 grid(blocks), block(threads);
-    if (args.fp32) {
-        if (args.trace)
-            hipLaunchKernelGGL((vsample_kernel<F, D, true, true>), grid, block, lds_bytes, stream, args);
-        else
-            hipLaunchKernelGGL((vsample_kernel<F, D, false, true>), grid, block, lds_bytes, stream, args);
-    } else {
-        if (args.trace)
-            hipLaunchKernelGGL((vsample_kernel<F, D, true, false>), grid, block, lds_bytes, stream, args);
-        else
-            hipLaunchKernelGGL((vsample_kernel<F, D, false, false>), grid, block, lds_bytes, stream, args);
+const void *sample_kernel_fd(int kind, bool fp32) {
+    switch (kind) {
+    case kTraced:
+        return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, true>)
+                    : reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, false>);
+    case kCopies:
+        return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, true>)
+                    : reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, false>);
+    case kSplit:
+        return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kSplit, true>)
+                    : reinterpret_cast<const void *>(&vsample_kernel<F, D, kSplit, false>);
+    default:
+        return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kPlain, true>)
+                    : reinterpret_cast<const void *>(&vsample_kernel<F, D, kPlain, false>);
     }
-    return hipGetLastError();
 }
 
 }  // namespace mcubes

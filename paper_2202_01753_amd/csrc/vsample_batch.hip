@@ -32,7 +32,7 @@ __device__ __forceinline__ void run_segment(Const<SampleArgs> &a, const BatchSeg
     int32_t step[D];  // blockDim in base g
     {
         uint32_t sd[D];
-        digits_of<D>((uint64_t)blockDim.x, g, sd);
+        digits_of32<D>(blockDim.x, g, a.gmagic, sd);
 #pragma unroll
         for (int j = 0; j < D; ++j) step[j] = (int32_t)sd[j];
     }
@@ -43,7 +43,10 @@ __device__ __forceinline__ void run_segment(Const<SampleArgs> &a, const BatchSeg
     const uint64_t t1 = min(((uint64_t)sg.t1 + 63u) & ~63ull, (uint64_t)a.m);
     uint64_t t = t0 + threadIdx.x;
     uint32_t dig[D];
-    digits_of<D>(t, g, dig);
+    if (t1 <= 0xFFFFFFFFull - kBatchMaxBlock)
+        digits_of32<D>((uint32_t)t, g, a.gmagic, dig);
+    else
+        digits_of<D>(t, g, dig);
     double sI = 0.0, cI = 0.0, sV = 0.0, cV = 0.0;
     bool bad = false;
     while (t < t1) {

@@ -3,56 +3,24 @@
 
 namespace mcubes {
 
-hipError_t launch_sample_f1(int dim, int blocks, int threads, size_t lds_bytes,
-                             hipStream_t stream, const SampleArgs &args) {
+const void *sample_kernel_f1(int dim, int kind, bool fp32) {
     switch (dim) {
-    case 1: return launch_sample_fd<1, 1>(blocks, threads, lds_bytes, stream, args);
-    case 2: return launch_sample_fd<1, 2>(blocks, threads, lds_bytes, stream, args);
-    case 3: return launch_sample_fd<1, 3>(blocks, threads, lds_bytes, stream, args);
-    case 4: return launch_sample_fd<1, 4>(blocks, threads, lds_bytes, stream, args);
-    case 5: return launch_sample_fd<1, 5>(blocks, threads, lds_bytes, stream, args);
-    case 6: return launch_sample_fd<1, 6>(blocks, threads, lds_bytes, stream, args);
-    case 7: return launch_sample_fd<1, 7>(blocks, threads, lds_bytes, stream, args);
-    case 8: return launch_sample_fd<1, 8>(blocks, threads, lds_bytes, stream, args);
-    case 9: return launch_sample_fd<1, 9>(blocks, threads, lds_bytes, stream, args);
-    case 10: return launch_sample_fd<1, 10>(blocks, threads, lds_bytes, stream, args);
-    case 11: return launch_sample_fd<1, 11>(blocks, threads, lds_bytes, stream, args);
-    case 12: return launch_sample_fd<1, 12>(blocks, threads, lds_bytes, stream, args);
-    case 13: return launch_sample_fd<1, 13>(blocks, threads, lds_bytes, stream, args);
-    case 14: return launch_sample_fd<1, 14>(blocks, threads, lds_bytes, stream, args);
-    case 15: return launch_sample_fd<1, 15>(blocks, threads, lds_bytes, stream, args);
-    case 16: return launch_sample_fd<1, 16>(blocks, threads, lds_bytes, stream, args);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-template <int F, int D>
-static const void *symbol(bool trace, bool fp32) {
-    if (fp32)
-        return trace ? reinterpret_cast<const void *>(&vsample_kernel<F, D, true, true>)
-                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, false, true>);
-    return trace ? reinterpret_cast<const void *>(&vsample_kernel<F, D, true, false>)
-                 : reinterpret_cast<const void *>(&vsample_kernel<F, D, false, false>);
-}
-
-const void *sample_kernel_f1(int dim, bool trace, bool fp32) {
-    switch (dim) {
-    case 1: return symbol<1, 1>(trace, fp32);
-    case 2: return symbol<1, 2>(trace, fp32);
-    case 3: return symbol<1, 3>(trace, fp32);
-    case 4: return symbol<1, 4>(trace, fp32);
-    case 5: return symbol<1, 5>(trace, fp32);
-    case 6: return symbol<1, 6>(trace, fp32);
-    case 7: return symbol<1, 7>(trace, fp32);
-    case 8: return symbol<1, 8>(trace, fp32);
-    case 9: return symbol<1, 9>(trace, fp32);
-    case 10: return symbol<1, 10>(trace, fp32);
-    case 11: return symbol<1, 11>(trace, fp32);
-    case 12: return symbol<1, 12>(trace, fp32);
-    case 13: return symbol<1, 13>(trace, fp32);
-    case 14: return symbol<1, 14>(trace, fp32);
-    case 15: return symbol<1, 15>(trace, fp32);
-    case 16: return symbol<1, 16>(trace, fp32);
+    case 1: return sample_kernel_fd<1, 1>(kind, fp32);
+    case 2: return sample_kernel_fd<1, 2>(kind, fp32);
+    case 3: return sample_kernel_fd<1, 3>(kind, fp32);
+    case 4: return sample_kernel_fd<1, 4>(kind, fp32);
+    case 5: return sample_kernel_fd<1, 5>(kind, fp32);
+    case 6: return sample_kernel_fd<1, 6>(kind, fp32);
+    case 7: return sample_kernel_fd<1, 7>(kind, fp32);
+    case 8: return sample_kernel_fd<1, 8>(kind, fp32);
+    case 9: return sample_kernel_fd<1, 9>(kind, fp32);
+    case 10: return sample_kernel_fd<1, 10>(kind, fp32);
+    case 11: return sample_kernel_fd<1, 11>(kind, fp32);
+    case 12: return sample_kernel_fd<1, 12>(kind, fp32);
+    case 13: return sample_kernel_fd<1, 13>(kind, fp32);
+    case 14: return sample_kernel_fd<1, 14>(kind, fp32);
+    case 15: return sample_kernel_fd<1, 15>(kind, fp32);
+    case 16: return sample_kernel_fd<1, 16>(kind, fp32);
     default: return nullptr;
     }
 }
