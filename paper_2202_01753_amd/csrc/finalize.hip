@@ -56,8 +56,6 @@ finalize_kernel(const double *__restrict__ part, double *__restrict__ hacc, int 
     }
 }
 
-__global__ void clear_flag_kernel(uint32_t *flag) { *flag = 0u; }
-
 __global__ void zero_kernel(double *p, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0.0;
@@ -70,11 +68,6 @@ hipError_t launch_finalize(const double *partials, double *hist_acc, int blocks,
     const int nhb = with_hist ? (nhist + kThreads - 1) / kThreads : 0;
     hipLaunchKernelGGL(finalize_kernel, dim3(nhb + 1), dim3(kThreads), 0, stream, partials,
                        hist_acc, blocks, nhist, hist_stride, nhb, flag, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_clear_flag(uint32_t *flag, hipStream_t stream) {
-    hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, stream, flag);
     return hipGetLastError();
 }
 

@@ -16,6 +16,62 @@ constexpr int kBatchBlock = 256;     // threads per workgroup of the batched ker
 constexpr int kBatchMaxBlock = 512;
 constexpr int kBatchMaxDim = 10;     // dimensions the batched kernel supports
 
+// A run whose steps between sampling passes (Weighted-Estimates,
+// Check-Convergence, Adjust-Bin-Bounds of Alg. 2) run on the device: its
+// state in the workspace, mirrored after every pass into page-locked host
+// memory that the host reads once the pass is over.  last is the index of
+// the run's last iteration: itmax - 1 until a pass ends the run earlier
+// (converged, or a non-finite value); every kernel of a later pass then does
+// nothing.
+struct RunState {
+    int32_t last;
+    int32_t status;   // kRunGoing, kRunConverged or kRunNonFinite
+    int32_t k;        // passes finished
+    uint32_t ticket;  // (fused runs) workgroups that are through with the pass that ended the run
+    double est[3];    // weighted estimate, its standard deviation, chi^2/dof after k passes
+    double pad2;
+};
+constexpr int32_t kRunGoing = 0, kRunConverged = 1, kRunNonFinite = 2;
+
+// The steps of Alg. 2 before a pass inside its own sampling launch (fused
+// runs): every workgroup adjusts the grid from the previous pass's histogram
+// by itself, into its LDS, and decides for itself whether the run has ended,
+// from the same data in the same order; workgroup 0 also writes both down.
+// A pass then costs one launch instead of two and nothing of the grid goes
+// through memory between the steps and the pass.  Pass n adds its
+// histogram into accumulator set n mod 3, reads set n-1 and clears set n+1 (which
+// pass n-1 read), and likewise its totals (two sets) and non-finite flag.
+struct FusedArgs {
+    int32_t refine;         // the previous pass collected contributions: adjust the grid
+    int32_t prev_blocks;    // workgroups of the previous pass (0: this is the first pass)
+    int32_t itmax;
+    const double *prev_partials;
+    double *prev_acc, *clear_acc;
+    uint32_t *prev_flag, *clear_flag;
+    double *next_grid;      // the adjusted grid (first pass: equal bins), written by workgroup 0
+    RunState *state;        // run state; iters after it
+    double *iters;
+    RunState *host;         // host mirror, its iters and grid (grid may be null)
+    double *host_iters, *host_grid;
+    double tau_rel, chi2_max, alpha;
+};
+// Up to which size a run is fused: bins (every workgroup adjusts all axes),
+// passes (one lane of a wave each) and samples per pass.  Per pass, steps in a
+// launch of their own against fused: d = 2, 1e4 samples, 100 bins 21.7 -> 14.9 us;
+// d = 3, 1e6, 500 bins 32.4 -> 30.3; d = 8, 1e5, 100 bins, FP32 25.4 -> 22.7;
+// d = 10, 1e6, 100 bins 39.7 -> 37.7; but d = 10, 5e5, 200 bins 34.3 -> 34.6, d = 6,
+// 4e6, 100 bins 51.5 -> 51.5 and d = 4, 8e6, 100 bins, FP32 54.3 -> 57.4.
+constexpr int kFusedMaxBins = 1600;
+constexpr int kFusedMaxPasses = 64;
+constexpr int64_t kFusedMaxSamples = int64_t(1) << 22;
+// Accumulators in use of each set: every workgroup reads them all before it
+// can sample (two instead of kHistAcc: d = 8, 1e5 samples 27.9 instead of 32.9 us
+// per pass; one: 28.9, for the additions that then meet in it).
+constexpr int kFusedAccs = 2;
+// Doubles of LDS the steps inside a launch need after the grid: C/E, r, P and
+// the old boundaries (d rows of nb + 1 each).
+constexpr size_t fused_scratch(int d, int nb) { return 4 * (size_t)d * (nb + 1); }
+
 // Everything the sampling kernel needs, passed by value so that the per-axis
 // constants arrive in scalar registers.
 struct SampleArgs {
@@ -54,6 +110,7 @@ struct SampleArgs {
     const int32_t *run_last;  // nullptr, or the last iteration of a run whose steps run on the
                               // device: a pass with iter beyond it does nothing
     int32_t sdig[kMaxDim];  // stride in base g, least significant digit first
+    FusedArgs fused;        // kFused
 };
 
 // Per-axis constants, in device memory (the kernels read them with scalar loads):
@@ -66,6 +123,7 @@ constexpr int kPlain = 0;   // one lane per sub-cube
 constexpr int kTraced = 1;  // kPlain with per-sample and per-cube records
 constexpr int kCopies = 2;  // 2^copy_shift copies of every histogram bin side by side
 constexpr int kSplit = 3;   // kCopies, and a sub-cube's samples over 2^lsplit neighbouring lanes
+constexpr int kFused = 4;   // kSplit (lsplit may be 0) with the steps before the pass inside (FusedArgs)
 
 // The sampling kernel of that kind, or nullptr.
 const void *sample_kernel(int integrand, int dim, int kind, bool fp32);
@@ -90,23 +148,6 @@ constexpr int kHistAcc = 8;
 hipError_t launch_finalize(const double *partials, double *hist_acc, int blocks, int nhist, int hist_stride,
                            int with_hist, uint32_t *flag, double *out, hipStream_t stream);
 
-// A run whose steps between sampling passes (Weighted-Estimates,
-// Check-Convergence, Adjust-Bin-Bounds of Alg. 2) run on the device: its
-// state in the workspace, mirrored after every pass into page-locked host
-// memory that the host reads once the pass is over.  last is the index of
-// the run's last iteration: itmax - 1 until a pass ends the run earlier
-// (converged, or a non-finite value); every kernel of a later pass then does
-// nothing.
-struct RunState {
-    int32_t last;
-    int32_t status;   // kRunGoing, kRunConverged or kRunNonFinite
-    int32_t k;        // passes finished
-    int32_t pad;
-    double est[3];    // weighted estimate, its standard deviation, chi^2/dof after k passes
-    double pad2;
-};
-constexpr int32_t kRunGoing = 0, kRunConverged = 1, kRunNonFinite = 2;
-
 // The decision after pass it of such a run.  iters holds I_0 .. I_{itmax-1},
 // then var_0 .. var_{itmax-1}, on the device; host_iters the same in the host
 // mirror (host, host_iters: mapped page-locked memory).
@@ -117,6 +158,7 @@ struct RunCtl {
     double *host_iters;
     int32_t it, itmax;
     double tau_rel, chi2_max;
+    int32_t all;              // nonzero: mirror every pass's results, not this one's alone
 };
 
 // Start of a device-steps run: the state (last = itmax - 1, nothing done) and
@@ -140,6 +182,10 @@ struct StepsArgs {
     double *host_grid;        // mapped host copy of the boundaries, or null
     double alpha;
     int32_t d, nb, one_d, nref;
+    // end of a fused run: the accumulator set and flag that its last pass read,
+    // to be cleared, and the grid mirrored whether it was adjusted or not
+    double *clear_acc;        // or null
+    uint32_t *clear_flag;
 };
 hipError_t launch_steps(const StepsArgs &args, hipStream_t stream);
 
@@ -156,8 +202,6 @@ constexpr int kDeviceStepsMaxBins = MC_DEVICE_STEPS_MAX_BINS;
 
 // Zeroes n doubles (the histogram accumulators, before a workspace's first pass).
 hipError_t launch_zero(double *p, size_t n, hipStream_t stream);
-
-hipError_t launch_clear_flag(uint32_t *flag, hipStream_t stream);
 
 // ---- batched sampling: many integrals in one persistent launch ----
 

@@ -30,6 +30,8 @@ namespace {
 
 // ------------------------------------------------------------------ launch geometry and workspace
 
+constexpr size_t kFlagBytes = 64;  // three flags, a whole number of doubles
+
 // A sampling launch: which kernel, its shape in adjusting and No-Adjust passes.
 struct Launch {
     int kind;                 // kPlain, kTraced, kCopies or kSplit
@@ -47,7 +49,15 @@ struct Geometry {
     int64_t g, m, p;
     Launch run, traced;       // of untraced and of traced passes
     int hist_stride;          // doubles per histogram accumulator (padded)
-    size_t off_consts, off_grid, off_tables, off_partials, off_hist, off_out, off_flag, off_run, total;
+    bool fusable;             // room for runs with the steps inside the sampling launches
+    size_t off_consts, off_grid, off_tables, off_hist, off_flag, off_out, off_grid2, off_run, off_partials,
+        partials_stride, total;
+    // accumulator set, non-finite flag and totals of pass n in a fused run (the
+    // first of each in others)
+    size_t hist_set(int n) const { return off_hist + sizeof(double) * kHistAcc * (size_t)hist_stride * (n % 3); }
+    size_t flag_set(int n) const { return off_flag + sizeof(uint32_t) * (n % 3); }
+    size_t partials_set(int n) const { return off_partials + partials_stride * (n % 2); }
+    size_t grid_set(int n) const { return n % 2 ? off_grid2 : off_grid; }
 };
 
 mc_status blocks_for(const void *fn, int threads, size_t lds, int64_t m, int requested, int *out) {
@@ -252,6 +262,10 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
     const size_t most_blocks = (size_t)std::max(std::max(G.run.blocks_adj, G.run.blocks_noadj),
                                                 std::max(G.traced.blocks_adj, G.traced.blocks_noadj));
+    // Fused runs (see FusedArgs) need three accumulator sets, two grids and
+    // two sets of totals.  The regions that mc_prepare fills lie where the
+    // sub-cubes, the passes and the workgroups do not move them.
+    G.fusable = d * nb <= kFusedMaxBins && pr->blocks == 0;
     size_t off = 0;
     const size_t real = f32 ? sizeof(float) : sizeof(double);
     G.off_consts = off;
@@ -260,19 +274,22 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     off = align_up(off + sizeof(double) * d * (nb + 1));
     G.off_tables = off;
     if (pr->integrand == MC_F_GAUSS_TABLES) off = align_up(off + real * (f32 ? kTablesLen32 : kTablesLen));
-    G.off_partials = off;
-    off = align_up(off + sizeof(double) * 4 * most_blocks);
-    // the kHistAcc histogram accumulators of adjusting passes, kept zero
-    // between passes
+    // the histogram accumulators of adjusting passes and, right after them, the
+    // non-finite flags, kept zero between runs
     G.off_hist = off;
-    off = align_up(off + sizeof(double) * kHistAcc * (size_t)G.hist_stride);
+    off += sizeof(double) * kHistAcc * (size_t)G.hist_stride * (G.fusable ? 3 : 1);
+    G.off_flag = off;
+    off = align_up(off + kFlagBytes);
     G.off_out = off;
     off = align_up(off + sizeof(double) * (4 + (size_t)d * nb));
-    G.off_flag = off;
-    off = align_up(off + sizeof(uint32_t));
+    G.off_grid2 = off;
+    if (G.fusable) off = align_up(off + sizeof(double) * d * (nb + 1));
     // a device-steps run's state and its per-iteration (I, var)
     G.off_run = off;
     off = align_up(off + sizeof(RunState) + sizeof(double) * 2 * (size_t)pr->itmax);
+    G.off_partials = off;
+    G.partials_stride = align_up(sizeof(double) * 4 * most_blocks);
+    off += G.partials_stride * (G.fusable ? 2 : 1);
     G.total = off;
     *geo = G;
     return MC_OK;
@@ -414,11 +431,10 @@ mc_status prepare(const mc_problem *pr, const Geometry &G, char *ws, hipStream_t
             HIP_TRY(hipMemcpyAsync(ws + G.off_tables, pr->tables, sizeof(double) * kTablesLen,
                                    hipMemcpyHostToDevice, stream));
     }
-    HIP_TRY(launch_clear_flag(reinterpret_cast<uint32_t *>(ws + G.off_flag), stream));
-    // the histogram accumulators start at zero; the finalize or steps kernel
-    // of each adjusting pass clears them again after reading them
+    // the histogram accumulators and the flags start at zero; whatever reads
+    // them after a pass clears them again
     HIP_TRY(launch_zero(reinterpret_cast<double *>(ws + G.off_hist),
-                        (size_t)kHistAcc * G.hist_stride, stream));
+                        (G.off_flag + kFlagBytes - G.off_hist) / sizeof(double), stream));
     HIP_TRY(hipStreamSynchronize(stream));
     return MC_OK;
 }
@@ -658,7 +674,7 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
     auto tail = [&](int it) -> hipError_t {
         const bool adjust = it < prob->ita;
         StepsArgs sa{};
-        sa.ctl = RunCtl{dst, iters, hm_dev, h_its_dev, it, itmax, prob->tau_rel, prob->chi2_max};
+        sa.ctl = RunCtl{dst, iters, hm_dev, h_its_dev, it, itmax, prob->tau_rel, prob->chi2_max, 0};
         sa.partials = partials;
         sa.blocks = pass_blocks(it);
         sa.hist_stride = G.hist_stride;
@@ -747,6 +763,146 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
     return MC_OK;
 }
 
+// Whether the steps of a device-steps run go into the sampling launches
+// themselves (FusedArgs), and the launch with the LDS they need.
+bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
+    if (!G.fusable || G.run.kind == kPlain || prob->itmax > kFusedMaxPasses || G.m * G.p > kFusedMaxSamples)
+        return false;
+    Launch L = G.run;
+    L.kind = kFused;
+    L.fn = sample_kernel(prob->integrand, prob->dim, kFused, is_fp32(prob));
+    if (!L.fn) return false;
+    // each workgroup adjusts every axis: with 256 threads those of three axes
+    // of 100 bins take 20.0 us per pass, with 512 17.1
+    if (!prob->threads && L.threads == 256 && prob->dim * prob->nbins > 256) {
+        L.threads = 512;
+        L.blocks_adj = L.blocks_noadj = (int)std::max<int64_t>(1, ((G.m << L.lsplit) + 511) / 512);
+    }
+    const size_t need = lds_bytes_of(prob->dim, prob->nbins, false, is_fp32(prob)) +
+                        sizeof(double) * fused_scratch(prob->dim, prob->nbins);
+    if (need > kLdsDynamicLimit) return false;
+    int cus = 0;
+    if (compute_units(&cus) != hipSuccess) return false;
+    for (int adj = 0; adj < 2; ++adj) {
+        size_t &lds = adj ? L.lds_adj : L.lds_noadj;
+        int &blocks = adj ? L.blocks_adj : L.blocks_noadj;
+        lds = std::max(lds, need);
+        int per_cu = 0;
+        if (allow_lds(L.fn, lds) != hipSuccess || occupancy(L.fn, L.threads, lds, &per_cu) != hipSuccess || per_cu < 1)
+            return false;
+        blocks = std::min(blocks, per_cu * cus);
+    }
+    *out = L;
+    return true;
+}
+
+// A fused run: pass n's launch does the steps that follow pass n - 1 and then
+// samples; one steps launch follows the last pass.  Without a target the whole
+// run is queued at once; with one, kAhead launches ahead of the last
+// decision seen in the mirror (a run that ends leaves that many launches
+// queued, which return at once).
+mc_status integrate_fused(const mc_problem *prob, const Geometry &G, const Launch &L, char *ws, hipStream_t s,
+                          mc_result *out, double *h_iters, double *h_grid) {
+    constexpr int kAhead = 3;
+    const int d = prob->dim, nb = prob->nbins, itmax = prob->itmax;
+    const size_t grid_len = (size_t)d * (nb + 1);
+    char *hbuf = nullptr, *dbuf = nullptr;
+    HIP_TRY(run_mirror(sizeof(RunState) + sizeof(double) * (2 * (size_t)itmax + grid_len), &hbuf, &dbuf));
+    RunState *hm = reinterpret_cast<RunState *>(hbuf), *hm_dev = reinterpret_cast<RunState *>(dbuf);
+    double *h_its = reinterpret_cast<double *>(hm + 1), *h_its_dev = reinterpret_cast<double *>(hm_dev + 1);
+    double *h_gr = h_its + 2 * (size_t)itmax, *h_gr_dev = h_its_dev + 2 * (size_t)itmax;
+    std::memset(static_cast<void *>(hm), 0, sizeof(RunState));
+    RunState *dst = reinterpret_cast<RunState *>(ws + G.off_run);
+    double *iters = reinterpret_cast<double *>(dst + 1);
+    auto dbl = [&](size_t off) { return reinterpret_cast<double *>(ws + off); };
+    auto u32 = [&](size_t off) { return reinterpret_cast<uint32_t *>(ws + off); };
+    // the grid of pass n is version min(n, ita)
+    auto version = [&](int n) { return std::min(n, prob->ita); };
+    SampleArgs a[2];
+    for (int adj = 0; adj < 2; ++adj) {
+        if (adj ? prob->ita > 0 : prob->ita < itmax) fill_args(prob, G, L, ws, 0, adj != 0, &a[adj]);
+    }
+    auto pass = [&](int n) -> hipError_t {
+        const bool adjust = n < prob->ita;
+        SampleArgs &p = a[adjust ? 1 : 0];
+        p.iter = (uint32_t)n;
+        p.grid = dbl(G.grid_set(version(n > 0 ? n - 1 : 0)));
+        p.partials = dbl(G.partials_set(n));
+        p.hist_acc = dbl(G.hist_set(n));
+        p.flag = u32(G.flag_set(n));
+        FusedArgs &z = p.fused;
+        z.refine = n > 0 && n - 1 < prob->ita ? 1 : 0;
+        z.prev_blocks = n > 0 ? L.blocks(n - 1 < prob->ita) : 0;
+        z.itmax = itmax;
+        z.prev_partials = dbl(G.partials_set(n + 1));
+        z.prev_acc = dbl(G.hist_set(n + 2));
+        z.clear_acc = dbl(G.hist_set(n + 1));
+        z.prev_flag = u32(G.flag_set(n + 2));
+        z.clear_flag = u32(G.flag_set(n + 1));
+        z.next_grid = dbl(G.grid_set(version(n)));
+        z.state = dst;
+        z.iters = iters;
+        z.host = hm_dev;
+        z.host_iters = h_its_dev;
+        z.host_grid = h_grid ? h_gr_dev : nullptr;
+        z.tau_rel = prob->tau_rel;
+        z.chi2_max = prob->chi2_max;
+        z.alpha = prob->alpha;
+        return launch_sample(L.fn, L.blocks(adjust), L.threads, L.lds(adjust), s, p);
+    };
+    auto last = [&]() -> hipError_t {
+        const bool adjust = itmax - 1 < prob->ita;
+        StepsArgs sa{};
+        sa.ctl = RunCtl{dst, iters, hm_dev, h_its_dev, itmax - 1, itmax, prob->tau_rel, prob->chi2_max, 1};
+        sa.partials = dbl(G.partials_set(itmax - 1));
+        sa.blocks = L.blocks(adjust);
+        sa.hist_stride = G.hist_stride;
+        sa.hist_acc = dbl(G.hist_set(itmax - 1));
+        sa.flag = u32(G.flag_set(itmax - 1));
+        sa.grid = dbl(G.grid_set(version(itmax - 1)));
+        sa.host_grid = h_grid ? h_gr_dev : nullptr;
+        sa.alpha = prob->alpha;
+        sa.d = d;
+        sa.nb = nb;
+        sa.one_d = prob->one_d;
+        sa.nref = adjust ? (prob->one_d ? 1 : d) : 0;
+        sa.clear_acc = dbl(G.hist_set(itmax + 1));  // pass itmax - 2's
+        sa.clear_flag = u32(G.flag_set(itmax + 1));
+        return launch_steps(sa, s);
+    };
+    HIP_TRY(allow_lds(L.fn, std::max(L.lds_adj, L.lds_noadj)));
+    const volatile RunState *v = hm;
+    hipError_t err = hipSuccess;
+    for (int n = 0; n <= itmax && err == hipSuccess && v->status == kRunGoing; ++n) {
+        err = n < itmax ? pass(n) : last();
+        if (!(prob->tau_rel > 0.0)) continue;
+        for (unsigned spin = 1; err == hipSuccess && n - v->k >= kAhead && v->status == kRunGoing; ++spin)
+            if (spin % 1024 == 0) {
+                const hipError_t q = hipStreamQuery(s);
+                if (q == hipSuccess && n - v->k >= kAhead && v->status == kRunGoing) err = hipErrorUnknown;
+                if (q != hipSuccess && q != hipErrorNotReady) err = q;
+            }
+    }
+    const hipError_t err2 = hipStreamSynchronize(s);
+    HIP_TRY(err);
+    HIP_TRY(err2);
+    if (v->status == kRunNonFinite) return MC_ENONFINITE;
+    const int k = v->k;
+    if (h_grid) std::memcpy(h_grid, h_gr, sizeof(double) * grid_len);
+    out->estimate = v->est[0];
+    out->error = v->est[1];
+    out->chi2_dof = v->est[2];
+    out->iterations = k;
+    out->converged = v->status == kRunConverged ? 1 : 0;
+    out->calls = (int64_t)k * G.m * G.p;
+    if (h_iters)
+        for (int i = 0; i < k; ++i) {
+            h_iters[2 * i] = h_its[i];
+            h_iters[2 * i + 1] = h_its[itmax + i];
+        }
+    return MC_OK;
+}
+
 // Whether a run keeps the steps between passes on the device: asked for, and
 // the bin adjustment's LDS holds nb.
 bool steps_on_device(const mc_problem *prob) {
@@ -769,7 +925,12 @@ mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *s
         st = prepare(prob, G, ws, s);
         if (st != MC_OK) return st;
     }
-    if (pinned && steps_on_device(prob)) return integrate_device(prob, G, ws, s, out, h_iters, h_grid, timing);
+    if (pinned && steps_on_device(prob)) {
+        // with timing the passes and the steps stay launches of their own
+        Launch L;
+        if (!timing && fused_launch(prob, G, &L)) return integrate_fused(prob, G, L, ws, s, out, h_iters, h_grid);
+        return integrate_device(prob, G, ws, s, out, h_iters, h_grid, timing);
+    }
 
     const int d = prob->dim, nb = prob->nbins;
     std::vector<double> grid((size_t)d * (nb + 1)), buf(4 + (size_t)d * nb);

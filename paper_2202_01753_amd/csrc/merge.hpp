@@ -4,7 +4,7 @@
 // decision that ends a device-steps run.
 #pragma once
 
-#include "estimate.hpp"
+#include "estimate_device.hpp"
 #include "internal.hpp"
 
 namespace mcubes {
@@ -23,7 +23,7 @@ __device__ __forceinline__ void two_sum_merge(double &s, double &c, double s2, d
 // The per-workgroup totals of a pass (per workgroup: I sum and compensation,
 // var sum and compensation) merged by one workgroup of kThreads in a fixed
 // order: each thread a strided subset in workgroup order, then a pairwise
-// tree; all merges TwoSum-compensated.  Thread 0 gets I and var.
+// tree; all merges TwoSum-compensated.  Every thread gets I and var.
 __device__ inline void pass_totals(const double *part, int blocks, double *I, double *V) {
     __shared__ double red[kThreads][4];
     const int tid = threadIdx.x;
@@ -45,10 +45,8 @@ __device__ inline void pass_totals(const double *part, int blocks, double *I, do
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        *I = red[0][0] + red[0][1];
-        *V = red[0][2] + red[0][3];
-    }
+    *I = red[0][0] + red[0][1];
+    *V = red[0][2] + red[0][3];
 }
 
 // Bin b of the histogram: its kHistAcc accumulators summed in order
@@ -64,31 +62,52 @@ __device__ __forceinline__ double take_bin(double *hacc, size_t b, int hist_stri
     return s + c;
 }
 
-// After pass c.it of a device-steps run: records (I, var), runs
-// Weighted-Estimates over the passes so far and Check-Convergence (the same
-// code and roundings as the host driver), ends the run if it converged or
-// the pass saw a non-finite value, and mirrors all of it to the host.
+// After pass c.it of a device-steps run, by one wavefront (every lane with the
+// same arguments): records (I, var), runs Weighted-Estimates over the passes so
+// far and Check-Convergence (the same roundings as the host driver), ends the
+// run if it converged or the pass saw a non-finite value, and mirrors all of it
+// to the host.
 __device__ inline void decide(const RunCtl &c, double I, double V, bool bad) {
     RunState *st = c.state;
-    const int it = c.it, k = it + 1;
-    c.iters[it] = I;
-    c.iters[c.itmax + it] = V;
-    double est[3] = {st->est[0], st->est[1], st->est[2]};
+    const int it = c.it, k = it + 1, lane = threadIdx.x & 63;
+    double Ii = I, Vi = V;  // lane i: pass i (the first 64)
+    if (lane < it) {
+        Ii = c.iters[lane];
+        Vi = c.iters[c.itmax + lane];
+    }
+    if (lane == 0) {
+        c.iters[it] = I;
+        c.iters[c.itmax + it] = V;
+    }
+    double est[3] = {0.0, INFINITY, NAN};
     int32_t status = kRunGoing;
     if (bad) {
         status = kRunNonFinite;
+        for (int i = 0; i < 3; ++i) est[i] = st->est[i];
     } else {
-        weighted_estimate(k, c.iters, c.iters + c.itmax, est);
+        if (k <= 64) {
+            wave_weighted_estimate(k, Ii, Vi, est);
+        } else {
+            __threadfence_block();  // lane 0's two stores
+            weighted_estimate(k, c.iters, c.iters + c.itmax, est);
+        }
         if (converged_after(k, est, c.tau_rel, c.chi2_max)) status = kRunConverged;
     }
+    if (c.host) {
+        // everything else first, k last: a host that sees k has the rest
+        __threadfence_block();
+        for (int i = c.all ? lane : it + lane; i <= it; i += 64) {
+            c.host_iters[i] = c.iters[i];
+            c.host_iters[c.itmax + i] = c.iters[c.itmax + i];
+        }
+        __threadfence_system();
+    }
+    if (lane != 0) return;
     st->k = k;
     st->status = status;
     for (int i = 0; i < 3; ++i) st->est[i] = est[i];
     if (status != kRunGoing) st->last = it;
     if (c.host) {
-        // everything else first, k last: a host that sees k has the rest
-        c.host_iters[it] = I;
-        c.host_iters[c.itmax + it] = V;
         c.host->status = status;
         for (int i = 0; i < 3; ++i) c.host->est[i] = est[i];
         if (status != kRunGoing) c.host->last = it;

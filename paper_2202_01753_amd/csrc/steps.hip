@@ -15,6 +15,7 @@
 // scan would stop.
 #include <cmath>
 
+#include "estimate_device.hpp"
 #include "internal.hpp"
 #include "merge.hpp"
 
@@ -126,7 +127,7 @@ __global__ void __launch_bounds__(256) run_init_kernel(RunState *st, double *gri
         st->last = itmax - 1;
         st->status = kRunGoing;
         st->k = 0;
-        st->pad = 0;
+        st->ticket = 0u;
         st->est[0] = 0.0;
         st->est[1] = INFINITY;
         st->est[2] = NAN;
@@ -142,8 +143,10 @@ __global__ void __launch_bounds__(256) run_init_kernel(RunState *st, double *gri
 // grid row j is rewritten in place (m-Cubes1D, j = 0: and copied to every
 // axis); host_grid, if not null, receives every boundary written to grid.
 // C may be E itself: it is read before E is written.
-__device__ __forceinline__ void adjust_axis(double *lds, const double *C, double *grid, double *host_grid, int j, int d,
-                            int nb, int one_d, double alpha) {
+// mirror_unmoved: the host copy holds nothing yet, so it gets an axis that keeps
+// its boundaries too.
+__device__ __forceinline__ void adjust_axis(double *lds, const double *C, double *grid, double *host_grid, int j,
+                                            int d, int nb, int one_d, double alpha, bool mirror_unmoved) {
     double *r = lds, *P = r + nb, *prev = P + nb + 1, *E = prev + nb + 1;
     __shared__ double wave_tmp[kRefineThreads / 64];
     const int tid = threadIdx.x;
@@ -202,6 +205,8 @@ __device__ __forceinline__ void adjust_axis(double *lds, const double *C, double
         if (host_grid)
             for (int i = tid; i <= nb; i += kRefineThreads) host_grid[(size_t)j * (nb + 1) + i] = E[i];
     }
+    if (mirror_unmoved && !moved && host_grid)
+        for (int i = tid; i <= nb; i += kRefineThreads) host_grid[(size_t)j * (nb + 1) + i] = prev[i];
     // m-Cubes1D: axis 0's boundaries, adjusted or not, on every axis
     if (one_d) {
         const double *src = moved ? E : prev;
@@ -219,7 +224,7 @@ __device__ __forceinline__ void adjust_axis(double *lds, const double *C, double
 __global__ void __launch_bounds__(kRefineThreads)
 refine_kernel(double *grid, const double *hist, int d, int nb, int one_d, double alpha) {
     extern __shared__ double lds[];
-    adjust_axis(lds, hist + (size_t)blockIdx.x * nb, grid, nullptr, blockIdx.x, d, nb, one_d, alpha);
+    adjust_axis(lds, hist + (size_t)blockIdx.x * nb, grid, nullptr, blockIdx.x, d, nb, one_d, alpha, false);
 }
 
 // Everything between pass it and the next of a device-steps run, in one
@@ -238,14 +243,20 @@ __global__ void __launch_bounds__(kRefineThreads) steps_kernel(const StepsArgs A
         for (int i = threadIdx.x; i < nb; i += kRefineThreads)
             C[i] = merge::take_bin(A.hist_acc, (size_t)j * nb + i, A.hist_stride);
         __syncthreads();
-        adjust_axis(lds, C, A.grid, A.host_grid, j, A.d, nb, A.one_d, A.alpha);
+        adjust_axis(lds, C, A.grid, A.host_grid, j, A.d, nb, A.one_d, A.alpha, A.clear_acc != nullptr);
         return;
+    }
+    if (A.clear_acc) {
+        for (int i = threadIdx.x; i < kHistAcc * A.hist_stride; i += kRefineThreads) A.clear_acc[i] = 0.0;
+        if (threadIdx.x == 0) *A.clear_flag = 0u;
+        if (A.nref == 0 && A.host_grid)
+            for (int i = threadIdx.x; i < A.d * (A.nb + 1); i += kRefineThreads) A.host_grid[i] = A.grid[i];
     }
     double I = 0.0, V = 0.0;
     merge::pass_totals(A.partials, A.blocks, &I, &V);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
         const bool bad = *A.flag != 0u;
-        *A.flag = 0u;
+        if (threadIdx.x == 0) *A.flag = 0u;
         merge::decide(A.ctl, I, V, bad);
     }
 }

@@ -21,6 +21,7 @@
 
 #include <type_traits>
 
+#include "fused.hpp"
 #include "internal.hpp"
 
 namespace mcubes {
@@ -910,12 +911,32 @@ __global__ void __launch_bounds__(kMaxBlock)
     __attribute__((amdgpu_waves_per_eu(kFixedWaves<F, D, KIND, F32> ? kFixedWaves<F, D, KIND, F32> : 1,
                                        kFixedWaves<F, D, KIND, F32> ? kFixedWaves<F, D, KIND, F32> : 8)))
     vsample_kernel(const SampleArgs a) {
-    constexpr bool TRACE = KIND == kTraced, SPLIT = KIND == kSplit, COPIES = SPLIT || KIND == kCopies;
+    constexpr bool TRACE = KIND == kTraced, FUSED = KIND == kFused, SPLIT = KIND == kSplit || FUSED;
+    constexpr bool COPIES = SPLIT || KIND == kCopies;
     constexpr bool LOV = !SPLIT && kLowInVgpr<F, D, F32>;
     if (a.run_last && (int64_t)a.iter > (int64_t)*a.run_last) return;  // the run has ended
     extern __shared__ double lds[];
     const LdsView<F32> v(lds, D, a.nb);
-    load_lds<D, F32>(a, v);
+    if constexpr (FUSED) {
+        const double *B;
+        if (fused::steps<D>(a, v.hist, &B)) return;
+        const int nb = a.nb, row = nb + 1;
+        if constexpr (F32) {
+            const float inv_nb = 1.0f / (float)nb;
+            for (int e = threadIdx.x; e < D * nb; e += blockDim.x) {
+                const int i = e + fused::row_of(e, inv_nb);  // row j starts j entries later in rows of nb + 1
+                v.grid[2 * e] = (float)B[i];
+                v.grid[2 * e + 1] = (float)(B[i + 1] - B[i]);
+            }
+        } else {
+            for (int e = threadIdx.x; e < D * row; e += blockDim.x) v.grid[e] = B[e];
+        }
+        __syncthreads();  // B lies where the histogram will
+        if (a.hist)
+            for (int i = threadIdx.x; i < D * nb * a.hist_copies; i += blockDim.x) v.hist[i] = 0.0;
+    } else {
+        load_lds<D, F32>(a, v);
+    }
     __syncthreads();
     // the per-axis constants are the same for every lane: read them with
     // scalar loads (constant address space) rather than from LDS, whose
@@ -956,7 +977,7 @@ __global__ void __launch_bounds__(kMaxBlock)
         // into accumulator blockIdx % kHistAcc (ordinary device memory, so the
         // hardware FP64 atomic add applies); bins it never reached are skipped
         const int n = D * a.nb;
-        double *acc = a.hist_acc + (size_t)(blockIdx.x % kHistAcc) * a.hist_stride;
+        double *acc = a.hist_acc + (size_t)(blockIdx.x & ((FUSED ? kFusedAccs : kHistAcc) - 1)) * a.hist_stride;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
             double h;
             if constexpr (COPIES) {
@@ -983,6 +1004,9 @@ const void *sample_kernel_fd(int kind, bool fp32) {
     case kCopies:
         return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, true>)
                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, false>);
+    case kFused:
+        return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kFused, true>)
+                    : reinterpret_cast<const void *>(&vsample_kernel<F, D, kFused, false>);
     case kSplit:
         return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kSplit, true>)
                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, kSplit, false>);

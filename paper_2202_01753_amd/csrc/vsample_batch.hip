@@ -11,7 +11,7 @@
 // order (so the totals do not depend on which workgroup took which segment),
 // and a third adjusts the grids of the integrals still in their adjusting
 // iterations, on the device, so that grids and histograms never leave it.
-#include "estimate.hpp"
+#include "estimate_device.hpp"
 #include "vsample.hpp"
 
 namespace mcubes {
@@ -167,28 +167,36 @@ __global__ void __launch_bounds__(kFinThreads) batch_finalize_kernel(const Batch
         two_sum_merge(sI, cI, s2, c2);
         two_sum_merge(sV, cV, v2, e2);
     }
+    const double I = sI + cI, V = sV + cV;  // in every lane
+    const bool bad = B.flags[item] != 0u;
+    const int k = (int)it.a.iter + 1;  // iterations including this one
+    double est[3] = {0.0, 0.0, NAN};
+    bool conv = false;
+    uint32_t state = bad ? kItemFailed : kItemRunning;
+    if (!bad) {
+        if (k <= 64) {
+            double Ii = I, Vi = V;  // lane i: iteration i
+            if (lane < k - 1) {
+                Ii = it.iters[lane];
+                Vi = it.iters[it.itmax + lane];
+            }
+            wave_weighted_estimate(k, Ii, Vi, est);
+        }
+        if (lane == 0) {
+            it.iters[k - 1] = I;
+            it.iters[it.itmax + k - 1] = V;
+            if (k > 64) weighted_estimate(k, it.iters, it.iters + it.itmax, est);
+            conv = converged_after(k, est, it.tau_rel, it.chi2_max);
+            if (conv || k >= it.itmax) state = kItemDone;
+        }
+    }
     if (lane != 0) return;
     double *o = it.out;
-    const double I = sI + cI, V = sV + cV;
-    const bool bad = B.flags[item] != 0u;
     o[0] = r[0] = I;
     o[1] = r[1] = V;
     o[2] = r[2] = bad ? 1.0 : 0.0;
     o[3] = 0.0;
     B.flags[item] = 0u;
-    double est[3] = {0.0, 0.0, NAN};
-    bool conv = false;
-    uint32_t state = kItemRunning;
-    if (bad) {
-        state = kItemFailed;
-    } else {
-        const int k = (int)it.a.iter + 1;  // iterations including this one
-        it.iters[k - 1] = I;
-        it.iters[it.itmax + k - 1] = V;
-        weighted_estimate(k, it.iters, it.iters + it.itmax, est);
-        conv = converged_after(k, est, it.tau_rel, it.chi2_max);
-        if (conv || k >= it.itmax) state = kItemDone;
-    }
     if (state != kItemRunning) *it.state = state;
     r[3] = est[0];
     r[4] = est[1];
@@ -244,10 +252,7 @@ batch_refine_kernel(const BatchItem *items, const int32_t *axis_item, double *co
         return;
     }
     const double S = total_s;
-    for (int i = threadIdx.x; i < nb; i += kRefThreads) {
-        const double s = r[i];
-        r[i] = s == 0.0 ? 0.0 : (s == S ? 1.0 : pow((1.0 - s / S) / log(S / s), alpha));
-    }
+    for (int i = threadIdx.x; i < nb; i += kRefThreads) r[i] = compressed_share(r[i], S, alpha);
     __syncthreads();
     if (threadIdx.x != 0) return;
     double R = 0.0;
