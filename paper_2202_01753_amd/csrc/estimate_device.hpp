@@ -55,15 +55,16 @@ __device__ inline void wave_weighted_estimate(int k, double I, double var, doubl
 }
 
 // Lepage's damped compression of a bin's share s of the axis total S (0 < S
-// finite): ((1 - s/S) / ln(S/s))^alpha, 0 for s = 0 and 1 for s = S.  On the
-// device, where many bins share few threads (fused and batched adjustment); the
+// finite): ((1 - s/S) / ln(S/s))^alpha, 0 for s = 0 and 1 for s = S.  ROOT32: the
 // usual exponent 3/2 as q sqrt(q), whose two roundings are within the power
-// function's own error at a tenth of its instructions.
-__device__ inline double compressed_share(double s, double S, double alpha) {
+// function's own error at a tenth of its instructions (where many bins share
+// few threads: fused and batched adjustment).
+template <bool ROOT32>
+__device__ __forceinline__ double compressed_share(double s, double S, double alpha) {
     if (s == 0.0) return 0.0;
     if (s == S) return 1.0;
     const double q = (1.0 - s / S) / log(S / s);
-    return alpha == 1.5 ? q * sqrt(q) : pow(q, alpha);
+    return ROOT32 && alpha == 1.5 ? q * sqrt(q) : pow(q, alpha);
 }
 
 }  // namespace mcubes

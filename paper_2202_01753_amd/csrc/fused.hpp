@@ -194,7 +194,7 @@ __device__ __forceinline__ bool steps(const SampleArgs &a, double *scratch, cons
         // Lepage's damped compression of each bin's share
         for (int e = tid; e < bins; e += nthr) {
             const double S = axis_sum[row_of(e, inv_nb)];
-            if (S > 0.0 && isfinite(S)) r[e] = compressed_share(r[e], S, z.alpha);
+            if (S > 0.0 && isfinite(S)) r[e] = compressed_share<true>(r[e], S, z.alpha);
         }
         __syncthreads();
         // running sums, made non-decreasing: P[0] = 0, P[i + 1] = r[0] + ... + r[i]

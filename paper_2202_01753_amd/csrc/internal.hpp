@@ -297,6 +297,5 @@ hipError_t launch_batch_finalize(const BatchArgs &args, hipStream_t stream);
 hipError_t launch_batch_refine(const BatchItem *items, const int32_t *axis_item,
                                double *const *next_grid, int n_axes, int max_nb,
                                hipStream_t stream);
-const void *batch_refine_symbol();
 
 }  // namespace mcubes

@@ -724,7 +724,6 @@ struct mc_server {
         }
         HIP_TRY(hipEventRecord(ev[buf][1], stream));
         HIP_TRY(launch_batch_finalize(A, stream));
-        HIP_TRY(allow_lds(batch_refine_symbol(), sizeof(double) * max_nb));
         HIP_TRY(launch_batch_refine(A.items, reinterpret_cast<const int32_t *>(step_base + L.axis_item),
                                     reinterpret_cast<double *const *>(step_base + L.next_grid), n_axes,
                                     max_nb, stream));
