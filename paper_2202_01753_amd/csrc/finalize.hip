@@ -36,24 +36,41 @@ using merge::kThreads;
 
 // Blocks [0, nhb): kThreads bins per block, each thread one bin's
 // accumulators summed in order into out and cleared for the next pass.
-// Block nhb: the totals (merge::pass_totals) and the non-finite flag.
+// Block nhb: the totals (merge::pass_totals) and the non-finite flag.  With a
+// counter (zero before and after), out is mapped host memory and the last
+// block through writes seq to *done, which the host waits for.
 __global__ void __launch_bounds__(kThreads)
 finalize_kernel(const double *__restrict__ part, double *__restrict__ hacc, int blocks, int nhist,
-                int hist_stride, int nhb, uint32_t *flag, double *out) {
+                int hist_stride, int nhb, uint32_t *flag, double *out, uint32_t *counter, uint32_t *done,
+                uint32_t seq) {
     if ((int)blockIdx.x < nhb) {
         const int b = blockIdx.x * kThreads + threadIdx.x;
         if (b < nhist) out[4 + b] = merge::take_bin(hacc, b, hist_stride);
-        return;
+    } else {
+        double I = 0.0, V = 0.0;
+        merge::pass_totals(part, blocks, &I, &V);
+        if (threadIdx.x == 0) {
+            out[0] = I;
+            out[1] = V;
+            out[2] = *flag ? 1.0 : 0.0;
+            out[3] = 0.0;
+            *flag = 0u;
+        }
     }
-    double I = 0.0, V = 0.0;
-    merge::pass_totals(part, blocks, &I, &V);
-    if (threadIdx.x == 0) {
-        out[0] = I;
-        out[1] = V;
-        out[2] = *flag ? 1.0 : 0.0;
-        out[3] = 0.0;
-        *flag = 0u;
+    if (!counter) return;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(counter, 1u) == gridDim.x - 1) {
+        *counter = 0u;
+        __threadfence_system();
+        *(volatile uint32_t *)done = seq;
     }
+}
+
+// The grid of a host-steps pass from mapped host memory into the workspace.
+__global__ void __launch_bounds__(kThreads) upload_kernel(const double *src, double *dst, int n) {
+    const int i = blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) dst[i] = src[i];
 }
 
 __global__ void zero_kernel(double *p, size_t n) {
@@ -64,10 +81,16 @@ __global__ void zero_kernel(double *p, size_t n) {
 }  // namespace
 
 hipError_t launch_finalize(const double *partials, double *hist_acc, int blocks, int nhist, int hist_stride,
-                           int with_hist, uint32_t *flag, double *out, hipStream_t stream) {
+                           int with_hist, uint32_t *flag, double *out, uint32_t *counter, uint32_t *done,
+                           uint32_t seq, hipStream_t stream) {
     const int nhb = with_hist ? (nhist + kThreads - 1) / kThreads : 0;
     hipLaunchKernelGGL(finalize_kernel, dim3(nhb + 1), dim3(kThreads), 0, stream, partials,
-                       hist_acc, blocks, nhist, hist_stride, nhb, flag, out);
+                       hist_acc, blocks, nhist, hist_stride, nhb, flag, out, counter, done, seq);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload(const double *src, double *dst, int n, hipStream_t stream) {
+    hipLaunchKernelGGL(upload_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, src, dst, n);
     return hipGetLastError();
 }
 

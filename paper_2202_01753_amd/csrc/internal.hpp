@@ -144,9 +144,14 @@ constexpr int kHistAcc = 8;
 // Reduces the per-workgroup totals in a fixed order and sums the histogram
 // accumulators in order into out = [I, var, flag, 0, hist...]; clears the
 // accumulators (for the next pass) and the flag.  (Runs whose steps between
-// passes are on the host.)
+// passes are on the host.)  With a counter in device memory (zero), out and
+// done are mapped host memory, and seq is written to *done once out is whole.
 hipError_t launch_finalize(const double *partials, double *hist_acc, int blocks, int nhist, int hist_stride,
-                           int with_hist, uint32_t *flag, double *out, hipStream_t stream);
+                           int with_hist, uint32_t *flag, double *out, uint32_t *counter, uint32_t *done,
+                           uint32_t seq, hipStream_t stream);
+
+// n doubles from mapped host memory src into device memory dst.
+hipError_t launch_upload(const double *src, double *dst, int n, hipStream_t stream);
 
 // The decision after pass it of such a run.  iters holds I_0 .. I_{itmax-1},
 // then var_0 .. var_{itmax-1}, on the device; host_iters the same in the host
