@@ -624,6 +624,13 @@ struct mc_server {
                 }
             }
             G[grp] = per_cu * cus;
+            // as much LDS as leaves that many workgroups resident, for copies
+            // of the histogram of the integrals that need less than the largest
+            const size_t most = (kLdsLimit / per_cu - 1024) / kOccLdsGranule * kOccLdsGranule;
+            int same = 0;
+            if (most > lds[grp] && most <= kLdsDynamicLimit && occupancy(kern, T[grp], most, &same) == MC_OK &&
+                same >= per_cu)
+                lds[grp] = most;
             int64_t cubes = 0;
             for (int i = first[grp]; i < first[grp + 1]; ++i) cubes += active[i]->m;
             const int64_t parts =
@@ -656,6 +663,13 @@ struct mc_server {
             double *grid = reinterpret_cast<double *>(ws + r->off_grid[r->cur]);
             sample_args(&r->prob, r->g, r->m, r->p, (uint32_t)r->launched, adjust, ws + r->off_consts,
                         grid, r->tables.empty() ? nullptr : ws + r->off_tables, &b.a);
+            if (adjust) {
+                // copies of the histogram side by side, as many as the group's LDS holds
+                const bool f32 = fp32_of(*r);
+                const size_t room = lds[r->group] - lds_bytes_of(r->prob.dim, r->prob.nbins, false, f32);
+                while (b.a.copy_shift < 4 && (sizeof(double) * dnb(*r) << (b.a.copy_shift + 1)) <= room) ++b.a.copy_shift;
+                b.a.hist_copies = 1 << b.a.copy_shift;
+            }
             b.grid = grid;
             b.out = reinterpret_cast<double *>(ws + r->off_out);
             b.iters = reinterpret_cast<double *>(ws + r->off_iters);

@@ -55,7 +55,7 @@ __device__ __forceinline__ void run_segment(Const<SampleArgs> &a, const BatchSeg
         // (plain, not volatile, constant loads: measured faster here, where
         // the cases' shared register allocation is set by other values; one
         // phase, raised priority for the first part of each sample)
-        cube_pass<F, D, false, F32, false, false, false, false, true>(a, v, (Const<real_t<F32>> *)a.consts, t, dig,
+        cube_pass<F, D, false, F32, false, false, false, false, true, true>(a, v, (Const<real_t<F32>> *)a.consts, t, dig,
                                                                       It, vt, bad);
         two_sum_add(sI, cI, It);
         two_sum_add(sV, cV, vt);
@@ -69,7 +69,9 @@ __device__ __forceinline__ void run_segment(Const<SampleArgs> &a, const BatchSeg
         // segment never reached are skipped
         double *dst = B.items[sg.item].out + 4;
         for (int i = threadIdx.x; i < D * a.nb; i += blockDim.x) {
-            const double h = v.hist[i];
+            double h = 0.0;
+            for (int c = 0; c < a.hist_copies; ++c)
+                h += v.hist[i * a.hist_copies + ((c + (int)threadIdx.x) & (a.hist_copies - 1))];
             if (h != 0.0) unsafeAtomicAdd(dst + i, h);
         }
     }
