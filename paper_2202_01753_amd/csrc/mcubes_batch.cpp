@@ -180,10 +180,13 @@ constexpr int kGroups = 2 * kKernels;
 constexpr size_t kConstsMax = sizeof(double) * kConstStride * kBatchMaxDim;
 
 // Segments per workgroup of a launch: the queue balances the workgroups to
-// within about one segment.
-constexpr int kSegsPerWg = 8;
-// Sub-cubes a segment should at least hold (one per thread of a workgroup, twice).
-constexpr int64_t kMinSegCubes = 2 * kBatchMaxBlock;
+// within about one segment.  Every segment also loads a grid, clears and adds
+// up a histogram: with eight, and down to 1024 sub-cubes, a served burst of 64
+// requests took 15.1 ms against 14.4, one of 12 4.03 against 3.60; three or
+// down to 8192 samples: no better.
+constexpr int kSegsPerWg = 4;
+// Samples a segment should at least hold.
+constexpr int64_t kMinSegSamples = 4096;
 
 // Element counts of one step's tables.
 struct StepCounts {
@@ -631,10 +634,12 @@ struct mc_server {
             if (most > lds[grp] && most <= kLdsDynamicLimit && occupancy(kern, T[grp], most, &same) == MC_OK &&
                 same >= per_cu)
                 lds[grp] = most;
-            int64_t cubes = 0;
-            for (int i = first[grp]; i < first[grp + 1]; ++i) cubes += active[i]->m;
+            int64_t samples = 0;  // (each at most 2^62: kept from overflowing)
+            for (int i = first[grp]; i < first[grp + 1]; ++i)
+                samples = std::min<int64_t>(samples + std::min<int64_t>(active[i]->m * active[i]->p, int64_t(1) << 40),
+                                            int64_t(1) << 50);
             const int64_t parts =
-                std::max<int64_t>(1, std::min<int64_t>((int64_t)kSegsPerWg * G[grp], cubes / kMinSegCubes));
+                std::max<int64_t>(1, std::min<int64_t>((int64_t)kSegsPerWg * G[grp], samples / kMinSegSamples));
             plan::split_work(cubes_of.data(), costs.data(), first[grp], first[grp + 1], parts, segs,
                              item_first.data());
             plan::largest_first(segs, costs.data(), seg_lo[grp], (int)segs.size(), order);
