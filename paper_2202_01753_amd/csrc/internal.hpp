@@ -98,6 +98,10 @@ struct SampleArgs {
     int32_t hist_copies;    // LDS histogram copies.  kPlain: 2 = lanes 32-63 of a wave add into a
                             // second; kCopies, kSplit: 2^copy_shift, side by side per bin
     int32_t copy_shift;
+    int32_t window;         // kStaged: bins a stratum of a slow axis can reach, at most
+    int32_t stage_shift;    // kStaged: log2 of the copies of a window's bins (2 to 5)
+    uint32_t block_cubes;   // kStaged: sub-cubes per block of the fast axes, g^K
+    uint32_t blocks_total;  // and blocks, g^NS
     int32_t lsplit;         // kSplit: a sub-cube's samples go over 2^lsplit neighbouring lanes
     double s;               // nb / g
     float s32;              // nb / g rounded to float (FP32 evaluation)
@@ -124,6 +128,19 @@ constexpr int kTraced = 1;  // kPlain with per-sample and per-cube records
 constexpr int kCopies = 2;  // 2^copy_shift copies of every histogram bin side by side
 constexpr int kSplit = 3;   // kCopies, and a sub-cube's samples over 2^lsplit neighbouring lanes
 constexpr int kFused = 4;   // kSplit (lsplit may be 0) with the steps before the pass inside (FusedArgs)
+constexpr int kStaged = 5;  // blocks of sub-cubes that share their slow axes' digits (adjusting passes)
+constexpr int kStagedUnit = 6;  // kStaged on the unit cube, whose points need no scaling
+// The slow axes of the staged kernels of a dimension (0: there is none).
+constexpr int staged_slow_axes(int integrand, int dim) {
+    return integrand == 0 ? 0 : dim == 5 || dim == 6 ? 2 : dim == 7 ? 3 : dim >= 8 && dim <= 10 ? 4 : 0;
+}
+// Waves per SIMD they are compiled for and launched at: six (two workgroups of
+// 768 threads per CU) in FP32 evaluation, one sample at a time, for the FP64
+// corner peak and the FP64 Gaussian at d = 5, which fit 80 registers without
+// spills; four (one of 1024) for the others.
+constexpr int staged_waves(int integrand, int dim, bool fp32) {
+    return fp32 || integrand == MC_F_CORNER_PEAK || (integrand == MC_F_GAUSS_PRODUCT && dim == 5) ? 6 : 4;
+}
 
 // The sampling kernel of that kind, or nullptr.
 const void *sample_kernel(int integrand, int dim, int kind, bool fp32);

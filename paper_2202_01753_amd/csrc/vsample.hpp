@@ -542,6 +542,18 @@ constexpr int kFixedWaves =
           : (F32 && F == 3 && D == 6) ? 6
                                       : 0;
 
+// The slow axes of a staged launch (the NS last): all sub-cubes that the
+// workgroup has in hand share their digits, so those are scalars, the grid in
+// LDS is the window of bins their stratum can reach, and the histogram that
+// window with 2^stage_shift copies of every bin side by side, lane by lane (32,
+// one per lane of a half-wave, where the LDS holds them).
+template <typename R, int NS>
+struct SlowAxes {
+    R c[NS ? NS : 1];              // the digits
+    uint32_t row[NS ? NS : 1];     // LDS address that grid entry 0 would have
+    uint32_t stage[NS ? NS : 1];   // this lane's copy of histogram entry 0, likewise
+};
+
 // All p samples of sub-cube t (digits dig): returns I_t and var_t, adds the bin
 // contributions to the LDS histogram when collecting them, and records the
 // cube in the trace when tracing.  PAIR: evaluate the samples two at a time
@@ -554,11 +566,14 @@ constexpr int kFixedWaves =
 // the one-sample path raises the wave's priority for the first part of each
 // sample (the pair path always does).
 template <int F, int D, bool TRACE, bool F32, bool PAIR, bool EARLY, bool LOV = false, bool GF = false,
-          bool PRIO = false, bool COPIES = false, bool SPLIT = false, typename A, typename CP>
+          bool PRIO = false, bool COPIES = false, bool SPLIT = false, int NS = 0, bool UNIT = false, typename A,
+          typename CP>
 __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP sC, uint64_t t,
-                                          const uint32_t (&dig)[D], double &It, double &vt,
-                                          bool &bad, const real_t<F32> *lov = nullptr) {
+                                          const uint32_t (&dig)[D - NS], double &It, double &vt,
+                                          bool &bad, const real_t<F32> *lov = nullptr,
+                                          const SlowAxes<real_t<F32>, NS> &slow = {}) {
     using R = real_t<F32>;
+    constexpr int K = D - NS;  // axes below K are each lane's own
     constexpr bool kBatchConsts = !F32 && (F == 1 || F == 3);  // see axis_consts
     constexpr int NBLK = (D + 1) / 2;                      // blocks in the counter layout
     constexpr int NUSED = F32 ? (D + 3) / 4 : NBLK;        // blocks this precision needs
@@ -566,13 +581,13 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     const int nb = a.nb, row = F32 ? nb : nb + 1, rec = 3 * D + 2;
     const R s = R(F32 ? a.s32 : a.s);
     const int last = nb - 1;
-    const R lastr = R(last);
+    const R lastr = R(last), nbr = R(nb);
     const uint32_t grid0 = lds_address(v.grid), row_bytes = (uint32_t)row * 8u;
     // from a grid entry to its bin's histogram entry (see above); with two
     // histogram copies the upper half of each wave adds into the second, so at
     // most half as many lanes add into one bin at once
     uint32_t to_hist = lds_address(v.hist) - grid0 - (F32 ? 0u : 8u * (D - 1));
-    if (!COPIES && a.hist_copies > 1 && (threadIdx.x & 32)) to_hist += (uint32_t)(D * nb) * 8u;
+    if (!COPIES && a.hist_copies > 1 && (threadIdx.x & 32)) to_hist += (uint32_t)((D - NS) * nb) * 8u;
     // COPIES: the copies of a bin lie next to each other (row, bin, copy), and a
     // lane adds into copy lane mod copies
     const uint32_t copy_sh = COPIES ? 3u + (uint32_t)a.copy_shift : 3u;
@@ -586,8 +601,19 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
 
     R cd[D];
 #pragma unroll
-    for (int j = 0; j < D; ++j) cd[j] = R(dig[j]);
-    const uint32_t thi = uniform_hi(t);
+    for (int j = 0; j < D; ++j) cd[j] = j < K ? R(dig[j]) : slow.c[j < K ? 0 : j - K];
+    const uint32_t stage_sh = 3u + (uint32_t)a.stage_shift;
+    auto row_address = [&](int j) { return j < K ? grid0 + j * row_bytes : slow.row[j < K ? 0 : j - K]; };
+    // what add_bin takes for bin i of axis j, whose grid cell is at `cell`
+    auto target_of = [&](int j, int i, uint32_t cell) -> uint32_t {
+        if (COPIES) return ((uint32_t)i << copy_sh) + lane_hist;
+        return j < K ? cell : slow.stage[j < K ? 0 : j - K] + ((uint32_t)i << stage_sh);
+    };
+    auto add_to = [&](uint32_t target, int j, double sq) {
+        if (j >= K) add_bin<D, F32, true>(target, 0u, j, sq);
+        else add_bin<D, F32, COPIES>(target, COPIES ? j * hist_row : to_hist, j, sq);
+    };
+    const uint32_t thi = NS ? 0u : uniform_hi(t);  // (staged launches: below 2^32)
     const PhiloxCube pc = philox_cube((uint32_t)t, a.iter, k0);
     const bool traced = TRACE && (int64_t)t >= a.t0 && (int64_t)t < a.t1;
 
@@ -615,18 +641,20 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const R z = (cd[j] + u) * s;
                 int i;
                 const R frac = bin_of(z, last, lastr, i);
-                const uint32_t cell = cell_address(grid0 + j * row_bytes, i);
-                target[j] = COPIES ? ((uint32_t)i << copy_sh) + lane_hist : cell;
+                const uint32_t cell = cell_address(row_address(j), i);
+                target[j] = target_of(j, i, cell);
                 R left, width;
                 read_cell(cell, left, width);
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
                 R xj;
-                if constexpr (LOV)
+                if constexpr (UNIT)
+                    xj = xu;  // lo = 0, span = 1: the product and the sum are exact
+                else if constexpr (LOV)
                     xj = rfma(cj[1], xu, lov[j]);
                 else
                     xj = rfma(cj[1], xu, cj[0]);
-                J = J * (width * cj[2]);
+                J = J * (width * (UNIT ? nbr : cj[2]));
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -661,7 +689,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) add_bin<D, F32, COPIES>(cell[j], COPIES ? j * hist_row : to_hist, j, sq);
+                    if (j < axes) add_to(cell[j], j, sq);
             }
         };
         {
@@ -720,9 +748,9 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     const R z = (cd[j] + uj) * s;
                     int i;
                     gf_frac[j] = bin_of(z, last, lastr, i);
-                    cell[j] = cell_address(grid0 + j * row_bytes, i);
+                    cell[j] = cell_address(row_address(j), i);
                     load_cell(cell[j], gf_left[j], gf_right[j]);
-                    if constexpr (COPIES) cell[j] = ((uint32_t)i << copy_sh) + lane_hist;
+                    cell[j] = target_of(j, i, cell[j]);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of their uses
                 if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
@@ -745,18 +773,20 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     const R z = (cd[j] + u) * s;
                     int i;
                     frac = bin_of(z, last, lastr, i);
-                    cell[j] = cell_address(grid0 + j * row_bytes, i);
+                    cell[j] = cell_address(row_address(j), i);
                     read_cell(cell[j], left, width);
-                    if constexpr (COPIES) cell[j] = ((uint32_t)i << copy_sh) + lane_hist;
+                    cell[j] = target_of(j, i, cell[j]);
                 }
                 const R xu = rfma(frac, width, left);
                 const auto cj = axis_consts<kBatchConsts>(sC, j);
                 R xj;
-                if constexpr (LOV)
+                if constexpr (UNIT)
+                    xj = xu;  // lo = 0, span = 1: the product and the sum are exact
+                else if constexpr (LOV)
                     xj = rfma(cj[1], xu, lov[j]);
                 else
                     xj = rfma(cj[1], xu, cj[0]);
-                J = J * (width * cj[2]);
+                J = J * (width * (UNIT ? nbr : cj[2]));
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -781,7 +811,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 const int axes = a.one_d ? 1 : D;
 #pragma unroll
                 for (int j = 0; j < D; ++j)
-                    if (j < axes) add_bin<D, F32, COPIES>(cell[j], COPIES ? j * hist_row : to_hist, j, sq);
+                    if (j < axes) add_to(cell[j], j, sq);
             }
             if (traced) {
                 double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -994,10 +1024,160 @@ __global__ void __launch_bounds__(kMaxBlock)
     }
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uniform(float x) { return __uint_as_float(uniform(__float_as_uint(x))); }
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double((int)uniform((uint32_t)__double2hiint(x)), (int)uniform((uint32_t)__double2loint(x)));
+}
+
+// A staged pass of one integral (large adjusting passes): the lattice as g^NS
+// blocks of g^K sub-cubes (K = D - NS), a block's sub-cubes in rounds of one per
+// lane.  Workgroup b takes the rounds [b T / B, (b + 1) T / B) of the T rounds of
+// all blocks, so it walks through one block after another; see SlowAxes.
+//
+// Bound: VALU issue.  With all axes alike (kPlain, kCopies with 4) the LDS set
+// the pace, whose FP64 atomics at random bins cost 26 to 33 cycles per wave
+// against 8.7 where no two lanes meet on a bank; here that is so on NS axes, whose
+// digits are scalars besides, and on the unit cube (UNIT) the points' scaling,
+// an identity there, is left out.  Per pass: d = 8 corner peak, 1e9 samples,
+// 500 bins 8310 -> 7700 us (FP64), 5877 -> 4653 (FP32 evaluation); d = 10, 4e8,
+// 400 bins 4602 -> 3977 (FP64); d = 9, 8e8, FP32 6415 -> 4980; d = 6 tables, 1e8
+// 1004 -> 976 (FP64), 638 -> 594 (FP32); FP64 Gaussian kernels 1.01 to 1.07.
+template <int F, int D, int NS, bool F32, bool UNIT>
+__global__ void __launch_bounds__(kMaxBlock)
+    __attribute__((amdgpu_waves_per_eu(staged_waves(F, D, F32), staged_waves(F, D, F32))))
+    vsample_staged_kernel(const SampleArgs a) {
+    using R = real_t<F32>;
+    constexpr int K = D - NS;
+    constexpr bool GF = F32 || kGridFirst<F, D, F32>;
+    if (a.run_last && (int64_t)a.iter > (int64_t)*a.run_last) return;  // the run has ended
+    extern __shared__ double lds[];
+    const int nb = a.nb, row = F32 ? nb : nb + 1, tid = threadIdx.x, nthr = blockDim.x;
+    const int W = a.window, wrow = F32 ? W : W + 1;
+    LdsView<F32> v(lds, K, nb);
+    double *sgrid = v.hist + K * nb * a.hist_copies;  // NS windows of the grid
+    double *stage = sgrid + NS * wrow;                // NS windows of copies of the histogram
+    load_lds<K, F32>(a, v);
+    const int ss = a.stage_shift, quarter = (1 << ss) >> 2;
+    for (int i = tid; i < (NS * W) << ss; i += nthr) stage[i] = 0.0;
+    volatile Const<R> *sC = (volatile Const<R> *)a.consts;
+    constexpr bool LOV = !UNIT && kLowInVgpr<F, D, F32>;
+    R lov[D];
+    if constexpr (LOV) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            lov[j] = sC[kConstStride * j];
+            asm volatile("" : "+v"(lov[j]));
+        }
+    }
+    const uint32_t g = (uint32_t)a.g, C = a.block_cubes, NR = uniform((C + nthr - 1) / nthr);
+    const uint64_t T = (uint64_t)a.blocks_total * NR;  // below 2^32 (host)
+    uint32_t r = uniform((uint32_t)(T * blockIdx.x / gridDim.x));
+    const uint32_t r1 = uniform((uint32_t)(T * (blockIdx.x + 1) / gridDim.x));
+    uint32_t sup = uniform(r / NR), rr = r - sup * NR;
+    const R s = R(F32 ? a.s32 : a.s);
+    double sI = 0.0, cI = 0.0, sV = 0.0, cV = 0.0;
+    bool bad = false;
+    const uint32_t lane_copy = (uint32_t)(tid & ((1 << ss) - 1)) << 3;
+    while (r < r1) {
+        SlowAxes<R, NS> slow;
+        int i0[NS];
+        uint32_t x = sup;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const uint32_t q = uniform(x / g), c = x - q * g;
+            x = q;
+            slow.c[j] = uniform(R(c));
+            i0[j] = (int)uniform((uint32_t)min((int)(slow.c[j] * s), nb - 1));
+            slow.row[j] = lds_address(sgrid + j * wrow) - (uint32_t)i0[j] * 8u;
+            slow.stage[j] = lds_address(stage + ((j * W) << ss)) - ((uint32_t)i0[j] << (3 + ss)) + lane_copy;
+        }
+        // the windows: entries i0 .. i0 + W (FP64: boundaries), beyond the last
+        // bin repeated (never read)
+        for (int e = tid; e < NS * wrow; e += nthr) {
+            const int j = e / wrow, k = e - j * wrow;
+            int first = i0[0];
+#pragma unroll
+            for (int q = 1; q < NS; ++q) first = j == q ? i0[q] : first;
+            const double *B = a.grid + (size_t)(K + j) * (nb + 1);
+            if constexpr (F32) {
+                const int b = min(first + k, nb - 1);
+                float2 *cell = reinterpret_cast<float2 *>(sgrid) + e;
+                *cell = make_float2((float)B[b], (float)(B[b + 1] - B[b]));
+            } else {
+                sgrid[e] = B[min(first + k, nb)];
+            }
+        }
+        __syncthreads();
+        const uint32_t n = min(NR - rr, r1 - r);
+        uint32_t tl = rr * (uint32_t)nthr + (uint32_t)tid;
+        uint32_t dig[K];
+        digits_of32<K>(tl, g, a.gmagic, dig);
+        const uint32_t t0 = sup * C;
+        for (uint32_t k = 0; k < n; ++k) {
+            if (tl < C) {
+                double It, vt;
+                cube_pass<F, D, false, F32, false, true, LOV, GF, GF, false, false, NS, UNIT>(
+                    a, v, sC, (uint64_t)(t0 + tl), dig, It, vt, bad, lov, slow);
+                two_sum_add(sI, cI, It);
+                two_sum_add(sV, cV, vt);
+            }
+            tl += (uint32_t)nthr;
+            odometer_add<K>(dig, a.sdig, g);
+        }
+        r += n;
+        rr = 0;
+        ++sup;
+        __syncthreads();
+        // the windows' sums into the accumulators: four threads per bin, each a
+        // quarter of the copies, from a different one on in neighbouring bins
+        // (of 32 copies no two lanes of a half-wave then meet on a bank)
+        double *acc = a.hist_acc + (size_t)(blockIdx.x % kHistAcc) * a.hist_stride;
+        for (int e = tid; e < NS * W * 4; e += nthr) {
+            const int bin = e >> 2;
+            double h = 0.0, *first_copy = stage + (bin << ss) + (e & 3) * quarter;
+            for (int k = 0; k < quarter; ++k) {
+                double *q = first_copy + ((k + bin) & (quarter - 1));
+                h += *q;
+                *q = 0.0;
+            }
+            h += __shfl_xor(h, 1, 64);
+            h += __shfl_xor(h, 2, 64);
+            const int j = bin / W;
+            int first = i0[0];
+#pragma unroll
+            for (int q = 1; q < NS; ++q) first = j == q ? i0[q] : first;
+            if ((e & 3) == 0 && h != 0.0) unsafeAtomicAdd(acc + (K + j) * nb + first + (bin - j * W), h);
+        }
+        // (the next block's windows end with a barrier before anything is added)
+    }
+    block_totals(sI, cI, sV, cV, bad, a.partials + 4 * (size_t)blockIdx.x, a.flag);
+    const int n = K * nb;
+    double *acc = a.hist_acc + (size_t)(blockIdx.x % kHistAcc) * a.hist_stride;
+    for (int i = tid; i < n; i += nthr) {
+        const double h = a.hist_copies > 1 ? v.hist[i] + v.hist[n + i] : v.hist[i];
+        if (h != 0.0) unsafeAtomicAdd(acc + i, h);
+    }
+}
+
+template <int F, int D, bool UNIT>
+const void *staged_kernel_fd(bool fp32) {
+    constexpr int NS = staged_slow_axes(F, D);
+    return fp32 ? reinterpret_cast<const void *>(&vsample_staged_kernel<F, D, NS, true, UNIT>)
+                : reinterpret_cast<const void *>(&vsample_staged_kernel<F, D, NS, false, UNIT>);
+}
+
 // The kernels of one integrand and dimension, as launch_sample takes them.
 template <int F, int D>
 const void *sample_kernel_fd(int kind, bool fp32) {
     switch (kind) {
+    case kStaged:
+        if constexpr (staged_slow_axes(F, D) > 0) return staged_kernel_fd<F, D, false>(fp32);
+        else return nullptr;
+    case kStagedUnit:
+        if constexpr (staged_slow_axes(F, D) > 0) return staged_kernel_fd<F, D, true>(fp32);
+        else return nullptr;
     case kTraced:
         return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, true>)
                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, false>);
