@@ -176,6 +176,12 @@ std::vector<double> axis_constants(const mc_problem *pr) {
     return c;
 }
 
+double first_jacobian(const mc_problem *pr) {
+    long double j0 = 1.0L;
+    for (int j = 0; j < pr->dim; ++j) j0 *= (long double)pr->nbins * (long double)(pr->hi[j] - pr->lo[j]);
+    return (double)j0;
+}
+
 // ------------------------------------------------------------------ host steps of Alg. 2
 
 void init_grid(int d, int nb, double *grid) {
@@ -278,6 +284,7 @@ void sample_args(const mc_problem *pr, int64_t g, int64_t m, int64_t p, uint32_t
     a->hist_copies = 1;
     a->s = (double)nb / (double)g;
     a->s32 = (float)a->s;
+    a->j0 = first_jacobian(pr);
     a->inv = 1.0 / (double)(m * p);
     a->pd = (double)p;
     a->inv_pm1 = 1.0 / (a->pd - 1.0);

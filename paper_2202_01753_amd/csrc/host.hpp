@@ -62,6 +62,9 @@ hipError_t compute_units(int *cus);
 hipError_t occupancy(const void *fn, int threads, size_t lds_bytes, int *per_cu);
 // Per-axis constants (kConstStride doubles per axis) in the layout the kernels read.
 std::vector<double> axis_constants(const mc_problem *pr);
+// The volume times nb^dim: every axis's bins and span, multiplied in extended
+// precision and rounded once.
+double first_jacobian(const mc_problem *pr);
 // The per-integral part of the sampling-kernel arguments (lattice, scales,
 // iteration, pointers into device memory); launch-specific fields are zero.
 void sample_args(const mc_problem *pr, int64_t g, int64_t m, int64_t p, uint32_t iter, bool adjust,

@@ -106,6 +106,7 @@ struct SampleArgs {
     double s;               // nb / g
     float s32;              // nb / g rounded to float (FP32 evaluation)
     int32_t fp32;           // nonzero: FP32 evaluation
+    double j0;              // FP64: the volume times nb^dim, the Jacobian's first factor
     double inv;             // 1 / (m p)
     double pd;              // p
     double inv_pm1;         // 1 / (p - 1)

@@ -317,19 +317,25 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     // that takes 40 at 2e4 samples.
     struct Key {
         int64_t maxcalls;
-        int32_t dev, integrand, dim, nbins, itmax, precision, blocks, threads, one_d, unit;
+        int32_t dev, integrand, dim, nbins, itmax, precision, blocks, threads, one_d, unit, spread;
         bool operator==(const Key &o) const {
             return maxcalls == o.maxcalls && dev == o.dev && integrand == o.integrand && dim == o.dim &&
                    nbins == o.nbins && itmax == o.itmax && precision == o.precision && blocks == o.blocks &&
-                   threads == o.threads && one_d == o.one_d && unit == o.unit;
+                   threads == o.threads && one_d == o.one_d && unit == o.unit && spread == o.spread;
         }
     };
     thread_local Key kept_key{};
     thread_local Geometry kept{};
     Key key{pr->maxcalls, 0, pr->integrand, pr->dim, pr->nbins, pr->itmax, pr->precision, pr->blocks, pr->threads,
-            pr->one_d, 1};
+            pr->one_d, 1, 0};
     for (int j = 0; j < pr->dim; ++j)
         if (pr->lo[j] != 0.0 || pr->hi[j] != 1.0) key.unit = 0;
+    // The FP64 kernels start a sample's Jacobian from the volume times nb^dim
+    // (SampleArgs::j0) and multiply it by the widths, which only makes it smaller.
+    // Where that start is beyond the range of doubles, or near its ends, the
+    // traced kernel, which multiplies axis by axis, takes the passes.
+    const double j0 = first_jacobian(pr);
+    if (!is_fp32(pr) && !(j0 > 1e-200 && j0 < 1e200)) key.spread = 1;
     HIP_TRY(hipGetDevice(&key.dev));
     if (kept.total && key == kept_key) {
         *geo = kept;
@@ -345,12 +351,13 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     G.noadj = G.traced = plain;
     G.traced.kind = kTraced;
     G.traced.fn = sample_kernel(pr->integrand, d, kTraced, f32);
-    st = copies_launch(pr, G.m, G.p, plain, &G.noadj);
-    if (st != MC_OK) return st;
+    if (key.spread)
+        G.noadj = G.traced;
+    else if ((st = copies_launch(pr, G.m, G.p, plain, &G.noadj)) != MC_OK)
+        return st;
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
     G.adj = G.noadj;
-    st = staged_launch(pr, G.g, G.m, &G.adj);
-    if (st != MC_OK) return st;
+    if (!key.spread && (st = staged_launch(pr, G.g, G.m, &G.adj)) != MC_OK) return st;
     int most = 1;
     for (const Launch *L : {&G.adj, &G.noadj, &G.traced}) most = std::max({most, L->blocks_adj, L->blocks_noadj});
     const size_t most_blocks = (size_t)most;
@@ -904,7 +911,7 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
 // Whether the steps of a device-steps run go into the sampling launches
 // themselves (FusedArgs), and the launch with the LDS they need.
 bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
-    if (!G.fusable || G.noadj.kind == kPlain || prob->itmax > kFusedMaxPasses || G.m * G.p > kFusedMaxSamples)
+    if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || prob->itmax > kFusedMaxPasses || G.m * G.p > kFusedMaxSamples)
         return false;
     Launch L = G.noadj;  // (passes this small are never staged)
     L.kind = kFused;

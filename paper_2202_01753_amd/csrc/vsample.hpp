@@ -130,6 +130,13 @@ __device__ __forceinline__ void philox_block(const PhiloxCube &q, uint32_t c, ui
     w[3] = x3;
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uniform(float x) { return __uint_as_float(uniform(__float_as_uint(x))); }
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double((int)uniform((uint32_t)__double2hiint(x)), (int)uniform((uint32_t)__double2loint(x)));
+}
+
 // (2X+1) 2^-53 for the 52-bit X = (whi << 20) | (wlo >> 12): the double with
 // exponent 0 and mantissa X is 1 + X 2^-52; subtracting 1 - 2^-53 is exact
 // (Sterbenz), so the result is exactly the open-interval uniform.
@@ -219,6 +226,21 @@ __device__ __forceinline__ float bin_of(float z, int, float lastf, int &i) {
     const float fz = rmin(rfloor(z), lastf);
     i = (int)fz;
     return fminf(fmaxf(z - fz, 0.0f), 1.0f);
+}
+
+// The same in FP64 for untraced passes: z clamped to zlast, the last double below
+// nb, first, after which one instruction (v_fract_f64) is z - floor(z), without the
+// conversion back.  The fraction differs from bin_of's only where z rounded up to
+// nb: 1 - 2^-44 (nb = 500) rather than 1.  With the Jacobian's one product per axis
+// (J0 in cube_pass), 12 instead of 18 issue cycles per sample and axis: d = 8
+// corner peak, 1e9 samples 7715 -> 7450 us; d = 9 Gaussian, 3e7, No-Adjust 271 -> 266;
+// a mixed batch of 192 (bin_below only) 9.81 -> 9.62 ms.  Passes that spread a
+// sub-cube over lanes (kSplit, kFused) are bound by latency and keep the above:
+// d = 10 tables, 1e6 samples 35.1 us against 35.5.
+__device__ __forceinline__ double bin_below(double z, double zlast, int &i) {
+    const double zb = __builtin_fmin(z, zlast);
+    i = (int)zb;
+    return __builtin_amdgcn_fract(zb);
 }
 
 // ---------------------------------------------------------------- integrands
@@ -566,8 +588,8 @@ struct SlowAxes {
 // the one-sample path raises the wave's priority for the first part of each
 // sample (the pair path always does).
 template <int F, int D, bool TRACE, bool F32, bool PAIR, bool EARLY, bool LOV = false, bool GF = false,
-          bool PRIO = false, bool COPIES = false, bool SPLIT = false, int NS = 0, bool UNIT = false, typename A,
-          typename CP>
+          bool PRIO = false, bool COPIES = false, bool SPLIT = false, int NS = 0, bool UNIT = false, bool J0 = false,
+          typename A, typename CP>
 __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP sC, uint64_t t,
                                           const uint32_t (&dig)[D - NS], double &It, double &vt,
                                           bool &bad, const real_t<F32> *lov = nullptr,
@@ -581,7 +603,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     const int nb = a.nb, row = F32 ? nb : nb + 1, rec = 3 * D + 2;
     const R s = R(F32 ? a.s32 : a.s);
     const int last = nb - 1;
-    const R lastr = R(last), nbr = R(nb);
+    const R lastr = R(last);
     const uint32_t grid0 = lds_address(v.grid), row_bytes = (uint32_t)row * 8u;
     // from a grid entry to its bin's histogram entry (see above); with two
     // histogram copies the upper half of each wave adds into the second, so at
@@ -602,6 +624,22 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
     R cd[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) cd[j] = j < K ? R(dig[j]) : slow.c[j < K ? 0 : j - K];
+    // the largest double below nb
+    const double zlast = uniform(__longlong_as_double(__double_as_longlong((double)nb) - 1));
+    // the bin of axis j and the fraction inside it
+    auto bin_at = [&](int j, const uint32_t *w, R &u, int &i) -> R {
+        if constexpr (F32) u = uniform24(w[j]);
+        else u = uniform53(w[j], w[D + j]);
+        const R z = (cd[j] + u) * s;
+        if constexpr (F32 || TRACE || SPLIT) return bin_of(z, last, lastr, i);
+        else return bin_below(z, zlast, i);
+    };
+    const R first_J = J0 ? R(a.j0) : R(1);
+    // the Jacobian: with J0 the volume and the bins are its first factor
+    auto times_width = [&](R J, R width, const auto &cj) -> R {
+        if constexpr (J0) return J * width;
+        else return J * (width * (UNIT ? R(nb) : cj[2]));
+    };
     const uint32_t stage_sh = 3u + (uint32_t)a.stage_shift;
     auto row_address = [&](int j) { return j < K ? grid0 + j * row_bytes : slow.row[j < K ? 0 : j - K]; };
     // what add_bin takes for bin i of axis j, whose grid cell is at `cell`
@@ -632,15 +670,12 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
             for (int b = 0; b < NUSED; ++b)
                 philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
-            R J = R(1);
+            R J = first_J;
 #pragma unroll
             for (int j = 0; j < D; ++j) {
                 R u;
-                if constexpr (F32) u = uniform24(w[j]);
-                else u = uniform53(w[j], w[D + j]);
-                const R z = (cd[j] + u) * s;
                 int i;
-                const R frac = bin_of(z, last, lastr, i);
+                const R frac = bin_at(j, w, u, i);
                 const uint32_t cell = cell_address(row_address(j), i);
                 target[j] = target_of(j, i, cell);
                 R left, width;
@@ -654,7 +689,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     xj = rfma(cj[1], xu, lov[j]);
                 else
                     xj = rfma(cj[1], xu, cj[0]);
-                J = J * (width * (UNIT ? nbr : cj[2]));
+                J = times_width(J, width, cj);
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -734,7 +769,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                 philox_block(pc, (uint32_t)(k * NBLK + b), thi, k0, k1, w + 4 * b);
             Integrand<F, D, R, EARLY> fx(a.tables);
             uint32_t cell[D];  // grid cells, or (COPIES) histogram entries
-            R J = R(1);
+            R J = first_J;
             // GF: every axis's bin and grid read first, then the rest axis by
             // axis, so that the grid reads are in flight together rather
             // than each waited for before the next is issued (see kGridFirst)
@@ -743,11 +778,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
                     R uj;
-                    if constexpr (F32) uj = uniform24(w[j]);
-                    else uj = uniform53(w[j], w[D + j]);
-                    const R z = (cd[j] + uj) * s;
                     int i;
-                    gf_frac[j] = bin_of(z, last, lastr, i);
+                    gf_frac[j] = bin_at(j, w, uj, i);
                     cell[j] = cell_address(row_address(j), i);
                     load_cell(cell[j], gf_left[j], gf_right[j]);
                     cell[j] = target_of(j, i, cell[j]);
@@ -768,11 +800,8 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     if constexpr (F32) width = gf_right[j];
                     else width = gf_right[j] - left;
                 } else {
-                    if constexpr (F32) u = uniform24(w[j]);
-                    else u = uniform53(w[j], w[D + j]);
-                    const R z = (cd[j] + u) * s;
                     int i;
-                    frac = bin_of(z, last, lastr, i);
+                    frac = bin_at(j, w, u, i);
                     cell[j] = cell_address(row_address(j), i);
                     read_cell(cell[j], left, width);
                     cell[j] = target_of(j, i, cell[j]);
@@ -786,7 +815,7 @@ __device__ __forceinline__ void cube_pass(const A &a, const LdsView<F32> &v, CP 
                     xj = rfma(cj[1], xu, lov[j]);
                 else
                     xj = rfma(cj[1], xu, cj[0]);
-                J = J * (width * (UNIT ? nbr : cj[2]));
+                J = times_width(J, width, cj);
                 fx.axis(j, xj, cj);
                 if (traced) {
                     double *r = a.trace + ((t - a.t0) * (uint64_t)a.p + k) * rec;
@@ -995,7 +1024,7 @@ __global__ void __launch_bounds__(kMaxBlock)
     while (t < (uint64_t)a.m) {
         double It, vt;
         cube_pass<F, D, TRACE, F32, kPairSamples<F, D, F32>, true, LOV, kGridFirst<F, D, F32>,
-                  kGridFirst<F, D, F32>, COPIES, SPLIT>(a, v, sC, t, dig, It, vt, bad, lov);
+                  kGridFirst<F, D, F32>, COPIES, SPLIT, 0, false, !F32 && !TRACE && !SPLIT>(a, v, sC, t, dig, It, vt, bad, lov);
         two_sum_add(sI, cI, It);
         two_sum_add(sV, cV, vt);
         // next sub-cube of this lane: t += stride, digit by digit
@@ -1024,13 +1053,6 @@ __global__ void __launch_bounds__(kMaxBlock)
     }
 }
 
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ float uniform(float x) { return __uint_as_float(uniform(__float_as_uint(x))); }
-__device__ __forceinline__ double uniform(double x) {
-    return __hiloint2double((int)uniform((uint32_t)__double2hiint(x)), (int)uniform((uint32_t)__double2loint(x)));
-}
-
 // A staged pass of one integral (large adjusting passes): the lattice as g^NS
 // blocks of g^K sub-cubes (K = D - NS), a block's sub-cubes in rounds of one per
 // lane.  Workgroup b takes the rounds [b T / B, (b + 1) T / B) of the T rounds of
@@ -1041,9 +1063,9 @@ __device__ __forceinline__ double uniform(double x) {
 // against 8.7 where no two lanes meet on a bank; here that is so on NS axes, whose
 // digits are scalars besides, and on the unit cube (UNIT) the points' scaling,
 // an identity there, is left out.  Per pass: d = 8 corner peak, 1e9 samples,
-// 500 bins 8310 -> 7700 us (FP64), 5877 -> 4653 (FP32 evaluation); d = 10, 4e8,
+// 500 bins 8310 -> 7450 us (FP64), 5877 -> 4653 (FP32 evaluation); d = 10, 4e8,
 // 400 bins 4602 -> 3977 (FP64); d = 9, 8e8, FP32 6415 -> 4980; d = 6 tables, 1e8
-// 1004 -> 976 (FP64), 638 -> 594 (FP32); FP64 Gaussian kernels 1.01 to 1.07.
+// 1004 -> 965 (FP64), 638 -> 594 (FP32); FP64 Gaussian kernels 1.01 to 1.07.
 template <int F, int D, int NS, bool F32, bool UNIT>
 __global__ void __launch_bounds__(kMaxBlock)
     __attribute__((amdgpu_waves_per_eu(staged_waves(F, D, F32), staged_waves(F, D, F32))))
@@ -1118,7 +1140,7 @@ __global__ void __launch_bounds__(kMaxBlock)
         for (uint32_t k = 0; k < n; ++k) {
             if (tl < C) {
                 double It, vt;
-                cube_pass<F, D, false, F32, false, true, LOV, GF, GF, false, false, NS, UNIT>(
+                cube_pass<F, D, false, F32, false, true, LOV, GF, GF, false, false, NS, UNIT, !F32>(
                     a, v, sC, (uint64_t)(t0 + tl), dig, It, vt, bad, lov, slow);
                 two_sum_add(sI, cI, It);
                 two_sum_add(sV, cV, vt);
