@@ -110,6 +110,38 @@ inline void split_work(const int64_t *m, const double *cost, int first, int last
     }
 }
 
+// The same with shares that shrink: `each` equal shares of the fraction
+// shares[0] of the work, then `each` of shares[1], and so on (the fractions add
+// up to 1).  At most (last - first) + each * levels pieces are appended.
+inline void split_work_shrinking(const int64_t *m, const double *cost, int first, int last, const double *shares,
+                                 int levels, int64_t each, std::vector<Piece> &out, int32_t *first_piece) {
+    double W = 0.0;
+    for (int i = first; i < last; ++i) W += (double)m[i] * cost[i];
+    int level = 0;
+    int64_t k = 1;                      // the next cut ends the k-th share of the level
+    double before = 0.0, start = 0.0;   // the work before the level, before the integral
+    for (int i = first; i < last; ++i) {
+        first_piece[i] = (int32_t)out.size();
+        const double end = start + (double)m[i] * cost[i];
+        int64_t t0 = 0;
+        while (level < levels) {
+            const double x = before + W * shares[level] * ((double)k / (double)each);
+            if (!(x < end)) break;
+            const int64_t t = std::min<int64_t>((int64_t)std::llround((x - start) / cost[i]), m[i]);
+            if (t > t0) {
+                out.push_back(Piece{i, t0, t});
+                t0 = t;
+            }
+            if (++k > each) {
+                before += W * shares[level++];
+                k = 1;
+            }
+        }
+        if (t0 < m[i]) out.push_back(Piece{i, t0, m[i]});
+        start = end;
+    }
+}
+
 // Indices lo..hi-1 of `pieces`, appended to order from the largest work to
 // the smallest, by a counting sort on the work quantised to 1/kOrderBuckets
 // of the largest piece's (equal buckets keep index order): linear in the

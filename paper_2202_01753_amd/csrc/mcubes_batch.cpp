@@ -179,13 +179,17 @@ constexpr int kGroups = 2 * kKernels;
 // axis at the batch's largest dimension).
 constexpr size_t kConstsMax = sizeof(double) * kConstStride * kBatchMaxDim;
 
-// Segments per workgroup of a launch: the queue balances the workgroups to
-// within about one segment.  Every segment also loads a grid, clears and adds
-// up a histogram: with eight, and down to 1024 sub-cubes, a served burst of 64
-// requests took 15.1 ms against 14.4, one of 12 4.03 against 3.60; three or
-// down to 8192 samples: no better.
-constexpr int kSegsPerWg = 4;
-// Samples a segment should at least hold.
+// Segments per workgroup of a launch and each one's fraction of the work.  The
+// queue hands them out largest first, so the workgroups end within about the
+// smallest; every segment also loads a grid, clears and adds up a histogram.
+// Sampling time of a mixed batch of 192 integrals (FP64, FP32), of 24 and of a
+// served burst of 64 requests: three shares of 0.6, 0.3, 0.1 9.54, 6.86, 1.88 and
+// 7.80 ms; four equal ones 9.88, 7.07, 2.02, 7.92; four of 0.4, 0.3, 0.2, 0.1 9.44, 6.76,
+// 2.00, 7.88; five down to 0.05 9.38, 6.74, 2.10, 8.05.
+constexpr double kSegShares[] = {0.6, 0.3, 0.1};
+constexpr int kSegsPerWg = 3;
+// Samples a segment should at least hold (2048 and eight segments per workgroup: a
+// served burst of 12 requests took 4.03 ms against 3.60; 8192: no better).
 constexpr int64_t kMinSegSamples = 4096;
 
 // Element counts of one step's tables.
@@ -640,8 +644,12 @@ struct mc_server {
                                             int64_t(1) << 50);
             const int64_t parts =
                 std::max<int64_t>(1, std::min<int64_t>((int64_t)kSegsPerWg * G[grp], samples / kMinSegSamples));
-            plan::split_work(cubes_of.data(), costs.data(), first[grp], first[grp + 1], parts, segs,
-                             item_first.data());
+            if (parts == (int64_t)kSegsPerWg * G[grp])
+                plan::split_work_shrinking(cubes_of.data(), costs.data(), first[grp], first[grp + 1], kSegShares,
+                                           kSegsPerWg, G[grp], segs, item_first.data());
+            else  // little work: as many segments as hold kMinSegSamples
+                plan::split_work(cubes_of.data(), costs.data(), first[grp], first[grp + 1], parts, segs,
+                                 item_first.data());
             plan::largest_first(segs, costs.data(), seg_lo[grp], (int)segs.size(), order);
         }
         seg_lo[kGroups] = (int)segs.size();
