@@ -364,7 +364,7 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     // Fused runs (see FusedArgs) need three accumulator sets, two grids and
     // two sets of totals.  The regions that mc_prepare fills lie where the
     // sub-cubes, the passes and the workgroups do not move them.
-    G.fusable = d * nb <= kFusedMaxBins && pr->blocks == 0;
+    G.fusable = d * nb <= kFusedMaxBins && pr->itmax <= kFusedMaxPasses && pr->blocks == 0;
     size_t off = 0;
     const size_t real = f32 ? sizeof(float) : sizeof(double);
     G.off_consts = off;
@@ -911,7 +911,7 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
 // Whether the steps of a device-steps run go into the sampling launches
 // themselves (FusedArgs), and the launch with the LDS they need.
 bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
-    if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || prob->itmax > kFusedMaxPasses || G.m * G.p > kFusedMaxSamples)
+    if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples)
         return false;
     Launch L = G.noadj;  // (passes this small are never staged)
     L.kind = kFused;
