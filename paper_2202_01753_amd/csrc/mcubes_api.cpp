@@ -176,7 +176,7 @@ double launch_worth(int waves, int copies, bool lds_bound) {
 // where there are fewer sub-cubes than lanes, a sub-cube's samples over
 // several lanes (kSplit), where it is worth more than the plain one, which
 // *out holds on entry.
-mc_status copies_launch(const mc_problem *pr, int64_t m, int64_t p, const Launch &plain, Launch *out) {
+mc_status copies_launch(const mc_problem *pr, int64_t g, int64_t m, int64_t p, const Launch &plain, Launch *out) {
     const int d = pr->dim, nb = pr->nbins;
     const bool f32 = is_fp32(pr);
     const size_t grid = lds_bytes_of(d, nb, false, f32), one = sizeof(double) * d * (size_t)nb;
@@ -207,6 +207,13 @@ mc_status copies_launch(const mc_problem *pr, int64_t m, int64_t p, const Launch
         }
     }
     if (best <= plain_worth) return MC_OK;
+    // One row of contributions (m-Cubes1D): copies only keep apart the lanes of a
+    // wave whose 64 strata of axis 0 lie in fewer than 12 bins (d = 2, 1e8 samples,
+    // 100 bins, FP32: 288 us against 517; 1e7, 300 bins, 8.6 bins per wave: 57 against
+    // 74); elsewhere their address arithmetic on every axis costs more (d = 8 corner peak,
+    // 1e9, FP32: 4950 against 4360 us; d = 4, 4.3e8 1480 against 1344; d = 3, 1e8, 17
+    // bins per wave: 318 against 302).  Passes that may be fused keep them.
+    if (pr->one_d && m * p > kFusedMaxSamples && 64 * (int64_t)nb >= 12 * g) return MC_OK;
     // Lanes: the resident ones.  Fewer sub-cubes than that: as many lanes per
     // sub-cube as still fit, each with a sample or more to do, and smaller
     // workgroups where the lanes would otherwise fill only some of the CUs
@@ -353,7 +360,7 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     G.traced.fn = sample_kernel(pr->integrand, d, kTraced, f32);
     if (key.spread)
         G.noadj = G.traced;
-    else if ((st = copies_launch(pr, G.m, G.p, plain, &G.noadj)) != MC_OK)
+    else if ((st = copies_launch(pr, G.g, G.m, G.p, plain, &G.noadj)) != MC_OK)
         return st;
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
     G.adj = G.noadj;
