@@ -364,6 +364,7 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
         return st;
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
     G.adj = G.noadj;
+    if (G.noadj.kind == kCopies && G.m * G.p > kFusedMaxSamples) G.noadj = plain;
     if (!key.spread && (st = staged_launch(pr, G.g, G.m, &G.adj)) != MC_OK) return st;
     int most = 1;
     for (const Launch *L : {&G.adj, &G.noadj, &G.traced}) most = std::max({most, L->blocks_adj, L->blocks_noadj});
