@@ -62,6 +62,12 @@ struct FusedArgs {
 // d = 10, 1e6, 100 bins 39.7 -> 37.7; but d = 10, 5e5, 200 bins 34.3 -> 34.6, d = 6,
 // 4e6, 100 bins 51.5 -> 51.5 and d = 4, 8e6, 100 bins, FP32 54.3 -> 57.4.
 constexpr int kFusedMaxBins = 1600;
+// The same for runs to a target, which may end after two passes and then have paid
+// every axis's steps in every workgroup three times (whole runs, fused against
+// launches of their own: d = 5, 134 bins 92 against 73 us; d = 6, 207 125 against
+// 99; d = 3, 430 131 against 122; but d = 2, 100 bins, twelve passes 210 against 256
+// and d = 3, 80 217 against 256).
+constexpr int kFusedTargetBins = 600;
 constexpr int kFusedMaxPasses = 64;
 constexpr int64_t kFusedMaxSamples = int64_t(1) << 22;
 // Accumulators in use of each set: every workgroup reads them all before it

@@ -921,6 +921,9 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
 bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
     if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples)
         return false;
+    // A run to a target may end after two passes, and then pays the steps of
+    // every axis in every workgroup three times
+    if (prob->tau_rel > 0.0 && prob->dim * prob->nbins > kFusedTargetBins) return false;
     Launch L = G.noadj;  // (passes this small are never staged)
     L.kind = kFused;
     L.fn = sample_kernel(prob->integrand, prob->dim, kFused, is_fp32(prob));
@@ -956,7 +959,7 @@ bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
 // queued, which return at once).
 mc_status integrate_fused(const mc_problem *prob, const Geometry &G, const Launch &L, char *ws, hipStream_t s,
                           mc_result *out, double *h_iters, double *h_grid) {
-    constexpr int kAhead = 3;
+    constexpr int kAhead = 2;
     const int d = prob->dim, nb = prob->nbins, itmax = prob->itmax;
     const size_t grid_len = (size_t)d * (nb + 1);
     char *hbuf = nullptr, *dbuf = nullptr;
