@@ -45,7 +45,7 @@ finalize_kernel(const double *__restrict__ part, double *__restrict__ hacc, int 
                 uint32_t seq) {
     if ((int)blockIdx.x < nhb) {
         const int b = blockIdx.x * kThreads + threadIdx.x;
-        if (b < nhist) out[4 + b] = merge::take_bin(hacc, b, hist_stride);
+        if (b < nhist) out[4 + b] = merge::take_bin<kHistAcc>(hacc, b, hist_stride);
     } else {
         double I = 0.0, V = 0.0;
         merge::pass_totals(part, blocks, &I, &V);

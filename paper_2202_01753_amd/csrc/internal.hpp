@@ -40,7 +40,8 @@ constexpr int32_t kRunGoing = 0, kRunConverged = 1, kRunNonFinite = 2;
 // A pass then costs one launch instead of two and nothing of the grid goes
 // through memory between the steps and the pass.  Pass n adds its
 // histogram into accumulator set n mod 3, reads set n-1 and clears set n+1 (which
-// pass n-1 read), and likewise its totals (two sets) and non-finite flag.
+// pass n-1 read), and likewise its totals (two sets) and non-finite flag.  A run
+// finds set 0 and flag 0 clear and leaves them so; the others it clears itself.
 struct FusedArgs {
     int32_t refine;         // the previous pass collected contributions: adjust the grid
     int32_t prev_blocks;    // workgroups of the previous pass (0: this is the first pass)
@@ -205,7 +206,8 @@ struct StepsArgs {
     const double *partials;   // the pass's per-workgroup totals
     int32_t blocks;           // workgroups of the pass
     int32_t hist_stride;
-    double *hist_acc;         // kHistAcc accumulators (cleared as they are read)
+    double *hist_acc;         // kHistAcc accumulators, or kFusedAccs at the end of a fused run (cleared
+                              // as they are read)
     uint32_t *flag;           // non-finite flag (read and cleared)
     double *grid;             // d*(nb+1) boundaries, adjusted in place
     double *host_grid;        // mapped host copy of the boundaries, or null

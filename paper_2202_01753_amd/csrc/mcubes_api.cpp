@@ -52,15 +52,20 @@ struct Geometry {
     Launch adj, noadj, traced;  // of adjusting and No-Adjust passes, and of traced ones of either
     const Launch &pass(bool adjust) const { return adjust ? adj : noadj; }
     int hist_stride;          // doubles per histogram accumulator (padded)
-    bool fusable;             // room for runs with the steps inside the sampling launches
-    size_t off_consts, off_grid, off_tables, off_hist, off_flag, off_out, off_grid2, off_run, off_partials,
-        partials_stride, total;
-    // accumulator set, non-finite flag and totals of pass n in a fused run (the
-    // first of each in others)
-    size_t hist_set(int n) const { return off_hist + sizeof(double) * kHistAcc * (size_t)hist_stride * (n % 3); }
+    bool fusable;             // runs may have their steps inside the sampling launches
+    size_t off_consts, off_grid, off_tables, off_hist, off_flag, off_out, off_run, off_partials, off_fused_grid,
+        off_fused_hist, off_fused_partials;
+    size_t total;             // what any run needs,
+    size_t total_fused;       // a fused one (if fusable),
+    size_t asked;             // and what the caller is told to provide
+    // accumulator set, non-finite flag, totals and grid of pass n in a fused
+    // run (the first of each in others)
+    size_t hist_set(int n) const {
+        return n % 3 ? off_fused_hist + sizeof(double) * kFusedAccs * (size_t)hist_stride * (n % 3 - 1) : off_hist;
+    }
     size_t flag_set(int n) const { return off_flag + sizeof(uint32_t) * (n % 3); }
-    size_t partials_set(int n) const { return off_partials + partials_stride * (n % 2); }
-    size_t grid_set(int n) const { return n % 2 ? off_grid2 : off_grid; }
+    size_t partials_set(int n) const { return n % 2 ? off_fused_partials : off_partials; }
+    size_t grid_set(int n) const { return n % 2 ? off_fused_grid : off_grid; }
 };
 
 mc_status blocks_for(const void *fn, int threads, size_t lds, int64_t m, int requested, int *out) {
@@ -369,10 +374,9 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     int most = 1;
     for (const Launch *L : {&G.adj, &G.noadj, &G.traced}) most = std::max({most, L->blocks_adj, L->blocks_noadj});
     const size_t most_blocks = (size_t)most;
-    // Fused runs (see FusedArgs) need three accumulator sets, two grids and
-    // two sets of totals.  The regions that mc_prepare fills lie where the
-    // sub-cubes, the passes and the workgroups do not move them.
-    G.fusable = d * nb <= kFusedMaxBins && pr->itmax <= kFusedMaxPasses && pr->blocks == 0;
+    // The regions that mc_prepare fills, or clears for the runs to keep clear,
+    // come first: the sub-cubes, the passes and the workgroups move none of
+    // them, so a prepared workspace serves runs with other iteration counts.
     size_t off = 0;
     const size_t real = f32 ? sizeof(float) : sizeof(double);
     G.off_consts = off;
@@ -384,20 +388,34 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     // the histogram accumulators of adjusting passes and, right after them, the
     // non-finite flags, kept zero between runs
     G.off_hist = off;
-    off += sizeof(double) * kHistAcc * (size_t)G.hist_stride * (G.fusable ? 3 : 1);
+    off += sizeof(double) * kHistAcc * (size_t)G.hist_stride;
     G.off_flag = off;
     off = align_up(off + kFlagBytes);
+    // From here on nothing is kept from one call to the next.
     G.off_out = off;
     off = align_up(off + sizeof(double) * (4 + (size_t)d * nb));
-    G.off_grid2 = off;
-    if (G.fusable) off = align_up(off + sizeof(double) * d * (nb + 1));
+    G.off_partials = off;
+    const size_t partials = align_up(sizeof(double) * 4 * most_blocks);
+    off += partials;
     // a device-steps run's state and its per-iteration (I, var)
     G.off_run = off;
-    off = align_up(off + sizeof(RunState) + sizeof(double) * 2 * (size_t)pr->itmax);
-    G.off_partials = off;
-    G.partials_stride = align_up(sizeof(double) * 4 * most_blocks);
-    off += G.partials_stride * (G.fusable ? 2 : 1);
-    G.total = off;
+    auto run_bytes = [](int itmax) { return align_up(sizeof(RunState) + sizeof(double) * 2 * (size_t)itmax); };
+    G.total = G.asked = off + run_bytes(pr->itmax);
+    // What fused runs (see FusedArgs) need besides: a second grid, two more
+    // accumulator sets and a second set of totals.  Asked for whatever the
+    // iteration count is (one workspace serves runs of any), so that more
+    // iterations never ask for less; a workspace without room is taken too, for
+    // runs that are not fused.
+    if (d * nb <= kFusedMaxBins && pr->blocks == 0) {
+        const size_t grid2 = align_up(sizeof(double) * d * (nb + 1));
+        const size_t hist2 = align_up(sizeof(double) * kFusedAccs * 2 * (size_t)G.hist_stride);
+        G.fusable = pr->itmax <= kFusedMaxPasses;
+        G.off_fused_grid = off + run_bytes(std::min(pr->itmax, kFusedMaxPasses));
+        G.off_fused_hist = G.off_fused_grid + grid2;
+        G.off_fused_partials = G.off_fused_hist + hist2;
+        G.total_fused = G.off_fused_partials + partials;
+        G.asked = std::max(G.total, G.total_fused);
+    }
     kept = G;
     kept_key = key;
     *geo = G;
@@ -642,7 +660,7 @@ mc_status mc_workspace_bytes(const mc_problem *prob, size_t *bytes) {
     Geometry G;
     mc_status st = geometry(prob, &G);
     if (st != MC_OK) return st;
-    *bytes = G.total;
+    *bytes = G.asked;
     return MC_OK;
 }
 
@@ -918,9 +936,9 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
 
 // Whether the steps of a device-steps run go into the sampling launches
 // themselves (FusedArgs), and the launch with the LDS they need.
-bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
-    if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples)
-        return false;
+bool fused_launch(const mc_problem *prob, const Geometry &G, size_t ws_bytes, Launch *out) {
+    if (!G.fusable || ws_bytes < G.total_fused) return false;
+    if ((G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples) return false;
     // A run to a target may end after two passes, and then pays the steps of
     // every axis in every workgroup three times
     if (prob->tau_rel > 0.0 && prob->dim * prob->nbins > kFusedTargetBins) return false;
@@ -1085,7 +1103,7 @@ mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *s
     if (pinned && steps_on_device(prob)) {
         // with timing the passes and the steps stay launches of their own
         Launch L;
-        if (!timing && fused_launch(prob, G, &L)) return integrate_fused(prob, G, L, ws, s, out, h_iters, h_grid);
+        if (!timing && fused_launch(prob, G, ws_bytes, &L)) return integrate_fused(prob, G, L, ws, s, out, h_iters, h_grid);
         return integrate_device(prob, G, ws, s, out, h_iters, h_grid, timing);
     }
 

@@ -49,13 +49,14 @@ __device__ inline void pass_totals(const double *part, int blocks, double *I, do
     *V = red[0][2] + red[0][3];
 }
 
-// Bin b of the histogram: its kHistAcc accumulators summed in order
-// (TwoSum) and cleared for the next pass.
+// Bin b of the histogram: its ACCS accumulators summed in order (TwoSum) and
+// cleared for the next pass.
+template <int ACCS>
 __device__ __forceinline__ double take_bin(double *hacc, size_t b, int hist_stride) {
     double *acc = hacc + b;
     double s = 0.0, c = 0.0;
 #pragma unroll
-    for (int x = 0; x < kHistAcc; ++x) {
+    for (int x = 0; x < ACCS; ++x) {
         two_sum_merge(s, c, acc[(size_t)x * hist_stride], 0.0);
         acc[(size_t)x * hist_stride] = 0.0;
     }

@@ -93,13 +93,14 @@ __global__ void __launch_bounds__(kRefineThreads) steps_kernel(const StepsArgs A
         const int j = blockIdx.x, nb = A.nb;
         double *C = lds + 3 * (size_t)nb + 2;  // the E array, free until the search
         for (int i = threadIdx.x; i < nb; i += kRefineThreads)
-            C[i] = merge::take_bin(A.hist_acc, (size_t)j * nb + i, A.hist_stride);
+            C[i] = A.clear_acc ? merge::take_bin<kFusedAccs>(A.hist_acc, (size_t)j * nb + i, A.hist_stride)
+                               : merge::take_bin<kHistAcc>(A.hist_acc, (size_t)j * nb + i, A.hist_stride);
         __syncthreads();
         adjust_axis(lds, C, A.grid, A.host_grid, j, A.d, nb, A.one_d, A.alpha, A.clear_acc != nullptr);
         return;
     }
     if (A.clear_acc) {
-        for (int i = threadIdx.x; i < kHistAcc * A.hist_stride; i += kRefineThreads) A.clear_acc[i] = 0.0;
+        for (int i = threadIdx.x; i < kFusedAccs * A.hist_stride; i += kRefineThreads) A.clear_acc[i] = 0.0;
         if (threadIdx.x == 0) *A.clear_flag = 0u;
         if (A.nref == 0 && A.host_grid)
             for (int i = threadIdx.x; i < A.d * (A.nb + 1); i += kRefineThreads) A.host_grid[i] = A.grid[i];
