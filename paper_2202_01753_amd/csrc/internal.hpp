@@ -138,6 +138,7 @@ constexpr int kSplit = 3;   // kCopies, and a sub-cube's samples over 2^lsplit n
 constexpr int kFused = 4;   // kSplit (lsplit may be 0) with the steps before the pass inside (FusedArgs)
 constexpr int kStaged = 5;  // blocks of sub-cubes that share their slow axes' digits (adjusting passes)
 constexpr int kStagedUnit = 6;  // kStaged on the unit cube, whose points need no scaling
+constexpr int kPerAxis = 7;  // kPlain whose Jacobian is multiplied axis by axis (FP64): see first_jacobian
 // The slow axes of the staged kernels of a dimension (0: there is none).
 constexpr int staged_slow_axes(int integrand, int dim) {
     return integrand == 0 ? 0 : dim == 5 || dim == 6 ? 2 : dim == 7 ? 3 : dim >= 8 && dim <= 10 ? 4 : 0;
@@ -149,6 +150,11 @@ constexpr int staged_slow_axes(int integrand, int dim) {
 constexpr int staged_waves(int integrand, int dim, bool fp32) {
     return fp32 || integrand == MC_F_CORNER_PEAK || (integrand == MC_F_GAUSS_PRODUCT && dim == 5) ? 6 : 4;
 }
+
+// Which of them a pass of the problem takes (adjust 1 or 0), or with run set the
+// passes of a whole run with the steps on the device: kFused, or the passes'
+// own; -1 for an invalid problem.  For the tests; not part of the C ABI.
+extern "C" int32_t mcubes_launch_kind(const mc_problem *prob, int32_t adjust, int32_t run);
 
 // The sampling kernel of that kind, or nullptr.
 const void *sample_kernel(int integrand, int dim, int kind, bool fp32);

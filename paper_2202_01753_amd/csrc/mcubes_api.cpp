@@ -119,13 +119,13 @@ mc_status pick_threads(const void *fn, size_t lds, int *out) {
     return MC_OK;
 }
 
-// The launch of one lane per sub-cube (kPlain; kTraced in its shape).
-mc_status plain_launch(const mc_problem *pr, int64_t m, Launch *out) {
+// The launch of one lane per sub-cube (kPlain or kPerAxis; kTraced in its shape).
+mc_status plain_launch(const mc_problem *pr, int kind, int64_t m, Launch *out) {
     const int d = pr->dim, nb = pr->nbins;
     const bool f32 = is_fp32(pr);
     Launch L{};
-    L.kind = kPlain;
-    L.fn = sample_kernel(pr->integrand, d, kPlain, f32);
+    L.kind = kind;
+    L.fn = sample_kernel(pr->integrand, d, kind, f32);
     if (!L.fn) return MC_EINVAL;
     L.lds_adj = lds_bytes_of(d, nb, true, f32);
     L.lds_noadj = lds_bytes_of(d, nb, false, f32);
@@ -342,10 +342,12 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
             pr->one_d, 1, 0};
     for (int j = 0; j < pr->dim; ++j)
         if (pr->lo[j] != 0.0 || pr->hi[j] != 1.0) key.unit = 0;
-    // The FP64 kernels start a sample's Jacobian from the volume times nb^dim
-    // (SampleArgs::j0) and multiply it by the widths, which only makes it smaller.
-    // Where that start is beyond the range of doubles, or near its ends, the
-    // traced kernel, which multiplies axis by axis, takes the passes.
+    // The FP64 kernels of large passes start a sample's Jacobian from the volume
+    // times nb^dim (SampleArgs::j0) and multiply it by the widths, which only makes
+    // it smaller.  Where that start is beyond the range of doubles, or near its
+    // ends, only kernels that multiply axis by axis take the passes (kPerAxis,
+    // kSplit and kFused; the traced kernel in their place: d = 8, 1e8 samples,
+    // 300 bins, No-Adjust 1076 us against kPerAxis's 865).
     const double j0 = first_jacobian(pr);
     if (!is_fp32(pr) && !(j0 > 1e-200 && j0 < 1e200)) key.spread = 1;
     HIP_TRY(hipGetDevice(&key.dev));
@@ -358,15 +360,13 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     const int d = pr->dim, nb = pr->nbins;
     const bool f32 = is_fp32(pr);
     Launch plain{};
-    st = plain_launch(pr, G.m, &plain);
+    st = plain_launch(pr, key.spread ? kPerAxis : kPlain, G.m, &plain);
     if (st != MC_OK) return st;
     G.noadj = G.traced = plain;
     G.traced.kind = kTraced;
     G.traced.fn = sample_kernel(pr->integrand, d, kTraced, f32);
-    if (key.spread)
-        G.noadj = G.traced;
-    else if ((st = copies_launch(pr, G.g, G.m, G.p, plain, &G.noadj)) != MC_OK)
-        return st;
+    if ((st = copies_launch(pr, G.g, G.m, G.p, plain, &G.noadj)) != MC_OK) return st;
+    if (key.spread && G.noadj.kind == kCopies) G.noadj = plain;  // (kSplit multiplies axis by axis)
     G.hist_stride = (int)((d * (size_t)nb + 31) / 32 * 32);
     G.adj = G.noadj;
     if (G.noadj.kind == kCopies && G.m * G.p > kFusedMaxSamples) G.noadj = plain;
@@ -1177,6 +1177,14 @@ mc_status mc_integrate_prepared(const mc_problem *prob, void *d_ws, size_t ws_by
                                 mc_result *out, double *h_iters, double *h_grid,
                                 mc_timing *timing) {
     return integrate(prob, d_ws, ws_bytes, stream, false, out, h_iters, h_grid, timing);
+}
+
+int32_t mcubes_launch_kind(const mc_problem *prob, int32_t adjust, int32_t run) {
+    Geometry G;
+    Launch L;
+    if (geometry(prob, &G) != MC_OK) return -1;
+    if (run && steps_on_device(prob) && fused_launch(prob, G, G.asked, &L)) return L.kind;
+    return G.pass(adjust != 0).kind;
 }
 
 }  // extern "C"

@@ -559,7 +559,7 @@ constexpr bool kLowInVgpr = F32 ? (F == 3 && D == 6) : ((F == 1 || F == 3) && D 
 // slower with it.
 template <int F, int D, int KIND, bool F32>
 constexpr int kFixedWaves =
-    KIND != kPlain && KIND != kCopies ? 0
+    KIND != kPlain && KIND != kPerAxis && KIND != kCopies ? 0
           : (!F32 && ((F == 1 && D >= 6 && D <= 8) || (F == 3 && (D == 6 || D == 7)))) ? 4
           : (F32 && F == 3 && D == 6) ? 6
                                       : 0;
@@ -972,6 +972,7 @@ __global__ void __launch_bounds__(kMaxBlock)
     vsample_kernel(const SampleArgs a) {
     constexpr bool TRACE = KIND == kTraced, FUSED = KIND == kFused, SPLIT = KIND == kSplit || FUSED;
     constexpr bool COPIES = SPLIT || KIND == kCopies;
+    constexpr bool J0 = !F32 && (KIND == kPlain || KIND == kCopies);
     constexpr bool LOV = !SPLIT && kLowInVgpr<F, D, F32>;
     if (a.run_last && (int64_t)a.iter > (int64_t)*a.run_last) return;  // the run has ended
     extern __shared__ double lds[];
@@ -1024,7 +1025,7 @@ __global__ void __launch_bounds__(kMaxBlock)
     while (t < (uint64_t)a.m) {
         double It, vt;
         cube_pass<F, D, TRACE, F32, kPairSamples<F, D, F32>, true, LOV, kGridFirst<F, D, F32>,
-                  kGridFirst<F, D, F32>, COPIES, SPLIT, 0, false, !F32 && !TRACE && !SPLIT>(a, v, sC, t, dig, It, vt, bad, lov);
+                  kGridFirst<F, D, F32>, COPIES, SPLIT, 0, false, J0>(a, v, sC, t, dig, It, vt, bad, lov);
         two_sum_add(sI, cI, It);
         two_sum_add(sV, cV, vt);
         // next sub-cube of this lane: t += stride, digit by digit
@@ -1203,6 +1204,8 @@ const void *sample_kernel_fd(int kind, bool fp32) {
     case kTraced:
         return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, true>)
                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, kTraced, false>);
+    case kPerAxis:
+        return fp32 ? nullptr : reinterpret_cast<const void *>(&vsample_kernel<F, D, kPerAxis, false>);
     case kCopies:
         return fp32 ? reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, true>)
                     : reinterpret_cast<const void *>(&vsample_kernel<F, D, kCopies, false>);
