@@ -89,16 +89,13 @@ __device__ __forceinline__ bool steps(const SampleArgs &a, double *scratch, cons
     const float inv_nb = 1.0f / (float)nb, inv_row = 1.0f / (float)row;
     double *E = scratch, *C = E, *r = E + total, *P = r + total, *prev = P + total;
 
-    // ended by the decision of an earlier launch (this one's own sets last to
-    // iter - 1, which every workgroup finds out by itself below)
-    const int it = (int)a.iter - 1;  // the pass the steps follow
-    if (it > 0 && *(volatile const int32_t *)&z.state->last < it) return true;
-    // the next pass's accumulators and flag, also before the first: the sets of
-    // passes 1 and 2 hold anything when a run starts
-    for (int i = blockIdx.x * nthr + tid; i < kFusedAccs * a.hist_stride; i += gridDim.x * nthr) z.clear_acc[i] = 0.0;
-    if (first_wg && tid == 0) *z.clear_flag = 0u;
-
+    // the next pass's accumulators and flag
+    auto clear_next = [&]() {
+        for (int i = blockIdx.x * nthr + tid; i < kFusedAccs * a.hist_stride; i += gridDim.x * nthr) z.clear_acc[i] = 0.0;
+        if (first_wg && tid == 0) *z.clear_flag = 0u;
+    };
     if (z.prev_blocks == 0) {  // the first pass: Init-Bins and the run's state
+        clear_next();  // (the sets of passes 1 and 2 hold anything when a run starts)
         for (int e = tid; e < total; e += nthr) {
             const double b = (double)(e - row * row_of(e, inv_row)) / (double)nb;
             E[e] = b;
@@ -119,6 +116,11 @@ __device__ __forceinline__ bool steps(const SampleArgs &a, double *scratch, cons
         return false;
     }
 
+    // ended by the decision of an earlier launch (this one's own sets last to
+    // iter - 1, which every workgroup finds out by itself below)
+    const int it = (int)a.iter - 1;  // the pass the steps follow
+    if (it > 0 && *(volatile const int32_t *)&z.state->last < it) return true;
+    clear_next();
     const int axes = z.refine ? (a.one_d ? 1 : D) : 0;
     const int bins = axes * nb;
     for (int e = tid; e < total; e += nthr) prev[e] = a.grid[e];
