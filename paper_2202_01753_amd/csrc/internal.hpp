@@ -64,11 +64,14 @@ struct FusedArgs {
 // 4e6, 100 bins 51.5 -> 51.5 and d = 4, 8e6, 100 bins, FP32 54.3 -> 57.4.
 constexpr int kFusedMaxBins = 1600;
 // The same for runs to a target, which may end after two passes and then have paid
-// every axis's steps in every workgroup three times (whole runs, fused against
-// launches of their own: d = 5, 134 bins 92 against 73 us; d = 6, 207 125 against
-// 99; d = 3, 430 131 against 122; but d = 2, 100 bins, twelve passes 210 against 256
-// and d = 3, 80 217 against 256).
-constexpr int kFusedTargetBins = 600;
+// every axis's steps in every workgroup three times.  Whole runs at 1e4, 1e5 and 1e6
+// samples (FP64), fused against launches of their own, of two passes: 100 bins 59, 68
+// and 85 us against 72, 69 and 75; 200 bins 65, 74, 87 against 69, 69, 75; 300 (d = 5)
+// 71, 76, 92 against 67, 68, 79; 600 (d = 5) 78, 82, 95 against 69, 69, 80.  Of twelve passes:
+// 100 bins 195, 234, 285 against 262, 259, 295; 200 bins 209, 238, 292 against 252, 259,
+// 303; 300 (d = 5) 236, 249, 327 against 264, 266, 323; 600 (d = 5) 267, 275, 338 against
+// 269, 273, 335.
+constexpr int kFusedTargetBins = 200;
 constexpr int kFusedMaxPasses = 64;
 constexpr int64_t kFusedMaxSamples = int64_t(1) << 22;
 // Accumulators in use of each set: every workgroup reads them all before it
