@@ -27,7 +27,7 @@ def test_runs_to_a_target_are_fused_up_to_200_bins(d, nb, tau, fused):
 TARGET = {
     "two passes": lambda **k: W.corner_peak(4, 14, maxcalls=200_000, nbins=50, itmax=12, tau_rel=1e-2, **k),
     "converges": lambda **k: W.corner_peak(4, 14, maxcalls=20_000, nbins=50, itmax=12, tau_rel=5e-4, **k),
-    "converges late": lambda **k: W.gauss_product(2, 15, maxcalls=5_000, nbins=100, itmax=40, tau_rel=3e-4, **k),
+    "converges late": lambda **k: W.gauss_product(2, 15, maxcalls=5_000, nbins=100, itmax=40, tau_rel=5e-4, **k),
     "target missed": lambda **k: W.gauss_product(3, 15, maxcalls=50_000, nbins=66, itmax=5, tau_rel=1e-7, **k),
     "no-adjust tail": lambda **k: W.gauss_product(3, 7, maxcalls=50_000, nbins=64, itmax=20, ita=2, tau_rel=3e-4, **k),
 }
