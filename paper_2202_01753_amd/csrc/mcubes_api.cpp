@@ -55,9 +55,7 @@ struct Geometry {
     bool fusable;             // runs may have their steps inside the sampling launches
     size_t off_consts, off_grid, off_tables, off_hist, off_flag, off_out, off_run, off_partials, off_fused_grid,
         off_fused_hist, off_fused_partials;
-    size_t total;             // what any run needs,
-    size_t total_fused;       // a fused one (if fusable),
-    size_t asked;             // and what the caller is told to provide
+    size_t total;
     // accumulator set, non-finite flag, totals and grid of pass n in a fused
     // run (the first of each in others)
     size_t hist_set(int n) const {
@@ -400,12 +398,10 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
     // a device-steps run's state and its per-iteration (I, var)
     G.off_run = off;
     auto run_bytes = [](int itmax) { return align_up(sizeof(RunState) + sizeof(double) * 2 * (size_t)itmax); };
-    G.total = G.asked = off + run_bytes(pr->itmax);
+    G.total = off + run_bytes(pr->itmax);
     // What fused runs (see FusedArgs) need besides: a second grid, two more
-    // accumulator sets and a second set of totals.  Asked for whatever the
-    // iteration count is (one workspace serves runs of any), so that more
-    // iterations never ask for less; a workspace without room is taken too, for
-    // runs that are not fused.
+    // accumulator sets and a second set of totals.  Counted whatever the iteration
+    // count is, so that a workspace for more iterations holds one for fewer.
     if (d * nb <= kFusedMaxBins && pr->blocks == 0) {
         const size_t grid2 = align_up(sizeof(double) * d * (nb + 1));
         const size_t hist2 = align_up(sizeof(double) * kFusedAccs * 2 * (size_t)G.hist_stride);
@@ -413,8 +409,7 @@ mc_status geometry(const mc_problem *pr, Geometry *geo) {
         G.off_fused_grid = off + run_bytes(std::min(pr->itmax, kFusedMaxPasses));
         G.off_fused_hist = G.off_fused_grid + grid2;
         G.off_fused_partials = G.off_fused_hist + hist2;
-        G.total_fused = G.off_fused_partials + partials;
-        G.asked = std::max(G.total, G.total_fused);
+        G.total = std::max(G.total, G.off_fused_partials + partials);
     }
     kept = G;
     kept_key = key;
@@ -660,7 +655,7 @@ mc_status mc_workspace_bytes(const mc_problem *prob, size_t *bytes) {
     Geometry G;
     mc_status st = geometry(prob, &G);
     if (st != MC_OK) return st;
-    *bytes = G.asked;
+    *bytes = G.total;
     return MC_OK;
 }
 
@@ -936,9 +931,9 @@ mc_status integrate_device(const mc_problem *prob, const Geometry &G, char *ws, 
 
 // Whether the steps of a device-steps run go into the sampling launches
 // themselves (FusedArgs), and the launch with the LDS they need.
-bool fused_launch(const mc_problem *prob, const Geometry &G, size_t ws_bytes, Launch *out) {
-    if (!G.fusable || ws_bytes < G.total_fused) return false;
-    if ((G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples) return false;
+bool fused_launch(const mc_problem *prob, const Geometry &G, Launch *out) {
+    if (!G.fusable || (G.noadj.kind != kCopies && G.noadj.kind != kSplit) || G.m * G.p > kFusedMaxSamples)
+        return false;
     // A run to a target may end after two passes, and then pays the steps of
     // every axis in every workgroup three times
     if (prob->tau_rel > 0.0 && prob->dim * prob->nbins > kFusedTargetBins) return false;
@@ -1103,7 +1098,7 @@ mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *s
     if (pinned && steps_on_device(prob)) {
         // with timing the passes and the steps stay launches of their own
         Launch L;
-        if (!timing && fused_launch(prob, G, ws_bytes, &L)) return integrate_fused(prob, G, L, ws, s, out, h_iters, h_grid);
+        if (!timing && fused_launch(prob, G, &L)) return integrate_fused(prob, G, L, ws, s, out, h_iters, h_grid);
         return integrate_device(prob, G, ws, s, out, h_iters, h_grid, timing);
     }
 
@@ -1183,7 +1178,7 @@ int32_t mcubes_launch_kind(const mc_problem *prob, int32_t adjust, int32_t run) 
     Geometry G;
     Launch L;
     if (geometry(prob, &G) != MC_OK) return -1;
-    if (run && steps_on_device(prob) && fused_launch(prob, G, G.asked, &L)) return L.kind;
+    if (run && steps_on_device(prob) && fused_launch(prob, G, &L)) return L.kind;
     return G.pass(adjust != 0).kind;
 }
 
