@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "host.hpp"
+#include "host_pool.hpp"
 #include "internal.hpp"
 
 using namespace mcubes;
@@ -465,32 +466,42 @@ struct Events {
     }
 };
 
-// Page-locked host memory of the calling thread, mapped for the device, grown
-// on demand and kept until the process ends.
+// Page-locked host memory, mapped for the device.
+struct MappedMemory {
+    static char *make(size_t bytes) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, bytes, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess)
+            return nullptr;
+        std::memset(p, 0, bytes);
+        return static_cast<char *>(p);
+    }
+    static bool free(char *p) { return hipHostFree(p) == hipSuccess; }
+};
+
+// Such memory of the calling thread (thread_local), grown on demand; a thread
+// that ends leaves it to later ones.
 struct Mapped {
     char *host = nullptr, *dev = nullptr;
-    size_t cap = 0;
+    HeldBuffer<MappedMemory> held;
     hipError_t reserve(size_t bytes) {
-        if (bytes > cap) {
-            if (host) {
-                const hipError_t e = hipHostFree(host);
-                host = nullptr;
-                cap = 0;
-                if (e != hipSuccess) return e;
-            }
-            const size_t want = std::max(bytes, size_t(1) << 16);
-            const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&host), want,
-                                               hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
-            if (e != hipSuccess) return e;
-            std::memset(host, 0, want);
-            cap = want;
-        }
+        host = held.reserve(bytes);
+        if (!host) return hipErrorOutOfMemory;
         void *d = nullptr;
         const hipError_t e = hipHostGetDevicePointer(&d, host, 0);
         dev = static_cast<char *>(d);
         return e;
     }
 };
+
+// Numbers of finalize launches, for the words that they write: different in
+// every thread's launches, since a buffer may come from another thread; never 0,
+// which fresh memory holds.
+uint32_t next_seq() {
+    static std::atomic<uint32_t> last{0};
+    uint32_t seq = last.fetch_add(1, std::memory_order_relaxed) + 1;
+    while (seq == 0) seq = last.fetch_add(1, std::memory_order_relaxed) + 1;
+    return seq;
+}
 
 // Waits until *word reads seq, with a look at the stream now and then, so
 // that an error or a stream that has run dry ends the wait.
@@ -531,7 +542,7 @@ mc_status run_pass(const mc_problem *pr, const Geometry &G, char *ws, hipStream_
     const size_t grid_bytes = sizeof(double) * d * (nb + 1);
     const size_t nout = 4 + (adjust ? (size_t)d * nb : 0);
     thread_local Mapped stage;
-    thread_local uint32_t seq = 0;
+    uint32_t seq = 0;
     double *grid_dev = reinterpret_cast<double *>(ws + G.off_grid);
     double *out_dev = reinterpret_cast<double *>(ws + G.off_out);
     uint32_t *counter = nullptr, *done = nullptr;
@@ -547,7 +558,7 @@ mc_status run_pass(const mc_problem *pr, const Geometry &G, char *ws, hipStream_
         out_map = reinterpret_cast<const double *>(stage.host + o_out);
         out_dev = reinterpret_cast<double *>(stage.dev + o_out);
         counter = reinterpret_cast<uint32_t *>(ws + G.off_flag + kCounterOffset);
-        seq += seq == 0xFFFFFFFFu ? 2 : 1;  // never 0, which fresh memory holds
+        seq = next_seq();
         HIP_TRY(launch_upload(reinterpret_cast<const double *>(stage.dev + o_grid), grid_dev, d * (nb + 1), stream));
     } else {
         HIP_TRY(hipMemcpyAsync(grid_dev, h_grid, grid_bytes, hipMemcpyHostToDevice, stream));
