@@ -589,6 +589,17 @@ mc_status run_pass(const mc_problem *pr, const Geometry &G, char *ws, hipStream_
     return out_host[2] != 0.0 ? MC_ENONFINITE : MC_OK;
 }
 
+// After a device error: what a call has queued still reads the calling thread's
+// page-locked memory and the caller's tables, so it is waited for before the
+// call returns the error.
+mc_status drained(mc_status st, hipStream_t stream) {
+    if (st == MC_EDEVICE) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipGetLastError();
+    }
+    return st;
+}
+
 // Fills a workspace: constants, tables, cleared accumulators and flags, queued
 // on the stream.  The constants go through page-locked memory of the calling
 // thread (mapped; else pageable copies) and the tables from the caller's, so
@@ -688,7 +699,8 @@ mc_status mc_prepare(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *
     mc_status st = geometry(prob, &G);
     if (st != MC_OK) return st;
     if (!d_ws || ws_bytes < G.total) return MC_EWORKSPACE;
-    return prepare(prob, G, static_cast<char *>(d_ws), static_cast<hipStream_t>(stream), true, true);
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    return drained(prepare(prob, G, static_cast<char *>(d_ws), s, true, true), s);
 }
 
 mc_status mc_sample_iteration(const mc_problem *prob, uint32_t iter, int32_t adjust,
@@ -707,9 +719,10 @@ mc_status mc_sample_iteration(const mc_problem *prob, uint32_t iter, int32_t adj
     }
     if (!d_ws || ws_bytes < G.total) return MC_EWORKSPACE;
     std::vector<double> out(4 + (size_t)d * nb);
-    st = run_pass(prob, G, static_cast<char *>(d_ws), static_cast<hipStream_t>(stream), iter,
-                  adjust != 0, h_grid, out.data(), static_cast<double *>(d_trace),
-                  d_trace ? t0 : 0, d_trace ? t1 : 0, nullptr, nullptr, nullptr);
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    st = drained(run_pass(prob, G, static_cast<char *>(d_ws), s, iter, adjust != 0, h_grid, out.data(),
+                          static_cast<double *>(d_trace), d_trace ? t0 : 0, d_trace ? t1 : 0, nullptr, nullptr, nullptr),
+                 s);
     if (st != MC_OK) return st;
     h_out[0] = out[0];
     h_out[1] = out[1];
@@ -1091,16 +1104,9 @@ bool steps_on_device(const mc_problem *prob) {
 
 // Alg. 2 on a workspace; upload: copy the constants and tables first
 // (otherwise a previous mc_prepare() of the same problem left them there).
-mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *stream, bool upload,
-                    mc_result *out, double *h_iters, double *h_grid, mc_timing *timing,
-                    bool pinned = true) {
-    if (!out) return MC_EINVAL;
-    Geometry G;
-    mc_status st = geometry(prob, &G);
-    if (st != MC_OK) return st;
-    if (!d_ws || ws_bytes < G.total) return MC_EWORKSPACE;
-    char *ws = static_cast<char *>(d_ws);
-    hipStream_t s = static_cast<hipStream_t>(stream);
+mc_status integrate_on(const mc_problem *prob, const Geometry &G, char *ws, hipStream_t s, bool upload,
+                       mc_result *out, double *h_iters, double *h_grid, mc_timing *timing, bool pinned) {
+    mc_status st;
     if (upload) {
         // (the passes that follow on the stream are waited for before this returns)
         st = prepare(prob, G, ws, s, pinned, false);
@@ -1168,6 +1174,18 @@ mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *s
         timing->lds_bytes = (int32_t)L.lds(prob->ita > 0);
     }
     return MC_OK;
+}
+
+mc_status integrate(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *stream, bool upload,
+                    mc_result *out, double *h_iters, double *h_grid, mc_timing *timing,
+                    bool pinned = true) {
+    if (!out) return MC_EINVAL;
+    Geometry G;
+    const mc_status st = geometry(prob, &G);
+    if (st != MC_OK) return st;
+    if (!d_ws || ws_bytes < G.total) return MC_EWORKSPACE;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    return drained(integrate_on(prob, G, static_cast<char *>(d_ws), s, upload, out, h_iters, h_grid, timing, pinned), s);
 }
 
 }  // namespace
