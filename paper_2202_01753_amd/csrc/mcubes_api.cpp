@@ -97,17 +97,23 @@ mc_status blocks_for(const void *fn, int threads, size_t lds, int64_t m, int req
 // Workgroup size when the problem leaves it open: of 1024, 768, 512 and 256
 // threads (whole multiples of four waves, so each of a CU's four SIMDs holds
 // the same number of every workgroup's waves), the one that keeps the most
-// waves resident per CU given the kernel's registers and the adjusting pass's
-// LDS; on a tie the larger, which means fewer workgroups and so fewer
-// histogram flushes.  768 is the d = 8 case: two 64 KB workgroups
-// of 12 waves fit where one of 16 did.
-mc_status pick_threads(const void *fn, size_t lds, int *out) {
+// waves resident given the kernel's registers, the adjusting pass's LDS and the
+// workgroups asked for, if any (d = 16 Gaussian, 2e7 samples, FP32, 64
+// workgroups, No-Adjust: 1.86 ms with 1024 threads, 2.72 with the 256 that keep most
+// resident on a full chip); on a tie the larger, which means fewer workgroups
+// and so fewer histogram flushes.  768 is the d = 8 case: two 64 KB
+// workgroups of 12 waves fit where one of 16 did.
+mc_status pick_threads(const void *fn, size_t lds, int requested, int *out) {
+    int cus = 0, best = 0;
+    HIP_TRY(compute_units(&cus));
     HIP_TRY(allow_lds(fn, lds));
-    int best = 0, best_waves = -1;
+    int64_t best_waves = -1;
     for (int t : {1024, 768, 512, 256}) {
         int per_cu = 0;
         HIP_TRY(occupancy(fn, t, lds, &per_cu));
-        const int waves = per_cu * t / 64;
+        int64_t resident = (int64_t)per_cu * cus;
+        if (requested > 0) resident = std::min<int64_t>(resident, requested);
+        const int64_t waves = resident * (t / 64);
         if (waves > best_waves) {
             best_waves = waves;
             best = t;
@@ -132,7 +138,7 @@ mc_status plain_launch(const mc_problem *pr, int kind, int64_t m, Launch *out) {
     if (pr->threads) {
         L.threads = pr->threads;
     } else {
-        st = pick_threads(L.fn, L.lds_adj, &L.threads);
+        st = pick_threads(L.fn, L.lds_adj, pr->blocks, &L.threads);
         if (st != MC_OK) return st;
     }
     // A second LDS copy of the histogram, for the upper half of each wave,
@@ -195,8 +201,11 @@ mc_status copies_launch(const mc_problem *pr, int64_t g, int64_t m, int64_t p, c
     if (!L.fn) return MC_EINVAL;
     double best = 0.0;
     for (int t : {1024, 768, 512, 256}) {
-        if (pr->threads && t != 1024) break;
-        const int threads = pr->threads ? pr->threads : t;
+        // (a given number of workgroups keeps the plain launch's threads: smaller
+        // ones would leave the problem fewer lanes)
+        const bool given = pr->threads || pr->blocks;
+        if (given && t != 1024) break;
+        const int threads = given ? plain.threads : t;
         for (int cs = 4; cs >= 2; --cs) {
             const size_t lds = grid + (one << cs);
             if (lds > kLdsDynamicLimit) continue;
@@ -228,7 +237,7 @@ mc_status copies_launch(const mc_problem *pr, int64_t g, int64_t m, int64_t p, c
     if (pr->blocks) resident = pr->blocks;
     while (L.lsplit < 6 && (2 << L.lsplit) <= p && m <= (resident * L.threads) >> (L.lsplit + 1)) ++L.lsplit;
     const int64_t lanes = m << L.lsplit;
-    if (!pr->threads) {
+    if (!pr->threads && !pr->blocks) {
         if (lanes <= (int64_t)cus * 256) L.threads = 256;
         else if (lanes <= (int64_t)cus * 512) L.threads = std::min(L.threads, 512);
     }

@@ -90,3 +90,14 @@ def test_cases_of_fused_runs_are_fused(case, precision):
     prob = _dev(F.CASES[case](seed=5, precision=precision))
     to_target = case in ("converges", "converges late", "target missed")  # (beyond 200 bins)
     assert _kind(prob, run=True) == (SPLIT if to_target else FUSED)
+
+
+@pytest.mark.parametrize("blocks", [1, 7, 64])
+@pytest.mark.parametrize("make,d,maxcalls,nb,precision", [
+    (W.corner_peak, 9, 5_429_903, 58, "fp32"), (W.gauss_product, 16, 20_280_379, 21, "fp32"),
+    (W.gauss_tables, 15, 183_386, 109, "fp64"), (W.gauss_product, 3, 132_288, 467, "fp64")])
+def test_few_workgroups_asked_for_are_the_largest(make, d, maxcalls, nb, precision, blocks):
+    # (one workgroup per CU at most: the most lanes are those of the largest workgroup)
+    bp = M.BoundProblem(make(d, 3, maxcalls=maxcalls, nbins=nb, itmax=2, seed=5, precision=precision), blocks=blocks)
+    for adjust in (True, False):
+        assert M.launch_shape(bp, adjust)[:2] == (blocks, 1024)
