@@ -60,10 +60,15 @@ class BufferPool {
         return true;
     }
 
-    void give(const HostBuffer &b) {
+    // (called as threads end: where the list cannot grow, the buffer is lost
+    // rather than the process)
+    void give(const HostBuffer &b) noexcept {
         if (!b.host) return;
-        std::lock_guard<std::mutex> lock(mu_);
-        free_.push_back(b);
+        try {
+            std::lock_guard<std::mutex> lock(mu_);
+            free_.push_back(b);
+        } catch (...) {
+        }
     }
 
     static constexpr size_t kLeast = size_t(1) << 16;
