@@ -517,10 +517,12 @@ def measure_single(args, M, torch, prob, precision, steps, warmup, exact, profil
     slots = slots_per_sample(p, gmp, adjust=p["ita"] > 0, fp32=fp32)
     achieved = slots * calls_per_iter / avg_launch_s
     r0 = timed[0]
+    # the kernel of an adjusting pass as the timed runs launch it (kinds 5 and 6: staged)
+    kernel = "vsample_staged_kernel" if M.lib().mcubes_launch_kind(bp.ref, 1, 0) in (5, 6) else "vsample_kernel"
     prof = (profiled(precision) if profiled_here else None) or {}
     roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
             "unit": "TOP/s", "op": SLOT_OP, "frac": achieved / VALU_PEAK_OPS, "traffic": prof.get("traffic"),
-            "kernel": "vsample_kernel" + (" (FP32-eval)" if fp32 else ""),
+            "kernel": kernel + (" (FP32-eval)" if fp32 else ""),
             "avg_launch_ms": avg_launch_s * 1e3, "ops_per_sample": ops, "slots_per_sample": slots,
             "launch": {"blocks": r0.blocks, "threads": r0.threads, "lds_bytes": r0.lds_bytes}}
     if "valu_insts_per_sample" in prof:

@@ -86,8 +86,9 @@ typedef struct mc_problem {
     int32_t blocks;          /* workgroups of the sampling kernel; 0 = fill the device */
     int32_t threads;         /* threads per workgroup, a multiple of 64 in 64..1024; 0: of 1024,
                                 768, 512 and 256 the one worth most by the waves it keeps
-                                resident per CU and the histogram copies its LDS holds
-                                (256 or 512 where there is less work than lanes) */
+                                resident (of the workgroups asked for, with blocks) and the
+                                histogram copies its LDS holds (without blocks 256 or 512
+                                where there is less work than lanes) */
     int32_t one_d;           /* 1: the m-Cubes1D variant (Sec. V): bin contributions of the first
                                 axis only, and its adjusted boundaries shared by every axis; meant
                                 for fully symmetric integrands.  0: separate grids per axis */
@@ -100,7 +101,8 @@ typedef struct mc_problem {
                                 Adjust-Bin-Bounds) on the device, so the passes of a run follow
                                 each other with no host round trip.  The bin adjustment takes the
                                 host's steps with its sums in a fixed order of its own and the
-                                device library's pow and log, so its boundaries agree with
+                                device library's pow and log (small runs without timing, see
+                                mc_timing: q sqrt(q) for alpha = 3/2), so its boundaries agree with
                                 mc_refine_grid's to rounding, not bit for bit.  Taken for
                                 nbins <= MC_DEVICE_STEPS_MAX_BINS; above that, and in
                                 mc_integrate_noalloc, the host runs the steps.  0: the host runs
@@ -123,7 +125,11 @@ typedef struct mc_result {
 } mc_result;
 
 /* Optional timing of mc_integrate, measured with HIP events on the call's
- * stream around each kernel launch. */
+ * stream around each kernel launch.  A timed run keeps its sampling passes and
+ * what lies between them in launches of their own; the same run without timing
+ * may do the steps between two passes inside the second one's launch (small
+ * passes with device_steps), with other workgroups and LDS, and its sums then
+ * differ by rounding. */
 typedef struct mc_timing {
     double sample_ms;    /* sum over iterations of the sampling kernel */
     double finalize_ms;  /* sum over iterations of the reduction kernel (with device_steps:
@@ -151,7 +157,9 @@ mc_status mc_workspace_bytes(const mc_problem *prob, size_t *bytes);
 /* The sampling kernel's launch for the problem on the current device:
  * workgroups, threads per workgroup and bytes of LDS per workgroup of a
  * V-Sample pass (adjust != 0) or a V-Sample-No-Adjust pass (adjust == 0), as
- * mc_integrate and mc_sample_iteration launch it.  Host query; no kernel
+ * mc_integrate with timing or with the steps on the host and an untraced
+ * mc_sample_iteration launch it (see mc_timing for the runs that launch
+ * otherwise; traced passes take a kernel of their own).  Host query; no kernel
  * runs.  MC_EINVAL for an invalid problem or a NULL output, MC_EDEVICE
  * without a usable device. */
 mc_status mc_launch_shape(const mc_problem *prob, int32_t adjust, int32_t *blocks, int32_t *threads,
@@ -173,7 +181,11 @@ mc_status mc_prepare(const mc_problem *prob, void *d_ws, size_t ws_bytes, void *
  *              records the sub-cubes t in [t0, t1): first (t1-t0)*p records
  *              of 3*dim+2 doubles (u_1..u_d, bin_1..bin_d, x_1..x_d, J, f)
  *              in the order (t, k), then (t1-t0) records of 2 doubles (I_t,
- *              var_t).  trace_bytes must hold them. */
+ *              var_t).  trace_bytes must hold them.  A traced pass takes the same
+ *              samples; in FP64 its Jacobian is multiplied axis by axis where an
+ *              untraced pass may start it from the volume times nbins^dim and
+ *              take a fraction of 1 in the last bin as 1 - 2^-44 or so, so that I,
+ *              var and the contributions differ by rounding. */
 mc_status mc_sample_iteration(const mc_problem *prob, uint32_t iter, int32_t adjust,
                               const double *h_grid, void *d_ws, size_t ws_bytes, void *stream,
                               double *h_out, double *h_hist, void *d_trace, size_t trace_bytes,
@@ -264,10 +276,11 @@ mc_status mc_integrate_noalloc(const mc_problem *prob, void *stream, mc_result *
  * pass (V-Sample or V-Sample-No-Adjust, per integral) of every active
  * integral in one persistent launch per group present (precision, and
  * whether the integral's LDS footprint limits workgroups per CU), merges each
- * integral's pieces in a fixed order, adjusts the grids of the integrals
- * still in their adjusting iterations on the device (the same steps as
- * mc_refine_grid, with the device library's pow and log), and then runs
- * Weighted-Estimates and Check-Convergence per integral on the host.  Grids,
+ * integral's pieces in a fixed order, runs Weighted-Estimates and
+ * Check-Convergence per integral and adjusts the grids of the integrals still
+ * in their adjusting iterations, all on the device (mc_refine_grid's steps with
+ * the sums in a fixed order of its own, the device library's log and pow, and
+ * q sqrt(q) for alpha = 3/2).  Grids,
  * histograms and tables stay in device memory.  Each integral's random
  * numbers depend only on its own seed, iteration, cube and sample, so an
  * integral gets the same samples alone and in any mix.

@@ -235,7 +235,8 @@ __device__ __forceinline__ float bin_of(float z, int, float lastf, int &i) {
 // The same in FP64 for untraced passes: z clamped to zlast, the last double below
 // nb, first, after which one instruction (v_fract_f64) is z - floor(z), without the
 // conversion back.  The fraction differs from bin_of's only where z rounded up to
-// nb: 1 - 2^-44 (nb = 500) rather than 1.  With the Jacobian's one product per axis
+// nb: 1 - 2^-44 (nb = 500) rather than 1, each within the rounding of z of the true
+// one, which lies below 1 (at 12 intervals one axis value in 2^53 or so).  With the Jacobian's one product per axis
 // (J0 in cube_pass), 12 instead of 18 issue cycles per sample and axis: d = 8
 // corner peak, 1e9 samples 7715 -> 7450 us; d = 9 Gaussian, 3e7, No-Adjust 271 -> 266;
 // a mixed batch of 192 (bin_below only) 9.81 -> 9.62 ms.  Passes that spread a
